@@ -93,7 +93,8 @@ typedef enum {
 typedef enum {
     OCTNCA_LAYOUT_AUTO = 0,  /* strips of 32 cells streamed over runs of 128 rows, shorter runs
                                 (down to 2 rows) on levels with fewer than 1024 such runs; two
-                                steps per launch (strips of 30) on levels with >= 2048 of those */
+                                steps per launch (strips of 30) on levels with >= 2048 of those;
+                                several steps per launch on tiles kept on chip, on small levels */
     OCTNCA_LAYOUT_ROWS = 1,  /* as AUTO, with two steps per launch wherever that kernel applies */
     OCTNCA_LAYOUT_TILES = 2  /* 16 x 32 cell tiles, one step per launch */
 } octnca_layout;
@@ -126,8 +127,8 @@ typedef struct {
     int32_t layout2d;    /* octnca_layout */
     int32_t steps_per_launch; /* 0: two steps per launch on 2D fp32 levels in the row layout
                                  with the OCTNCA_MLP_F16S arithmetic (the state between the
-                                 two steps stays on chip; same result bit for bit), one
-                                 elsewhere; 1: always one */
+                                 two steps stays on chip; same result bit for bit), several
+                                 (up to 10) on small 2D levels, one elsewhere; 1: always one */
 } octnca_model;
 
 typedef struct {
@@ -181,10 +182,11 @@ int octree_nca_upsample(const octnca_model *model, const void *coarse_state,
  * S3, Listing 1), out of place, alternating between two buffers: launch k
  * reads bufs[k % 2] and writes bufs[(k+1) % 2].  A launch runs one step, or
  * two (t, t+1) where model->steps_per_launch allows it and the level runs the
- * 2D fp32 row layout; the state after step t then stays on chip and the
- * result is the same bit for bit.  The number of two-step launches is kept
- * even, so the final state is in buf1 exactly when `steps` is odd, whatever
- * kernels run and on whatever device.
+ * 2D fp32 row layout, or several on a small 2D level; the states between the
+ * steps of a launch then stay on chip and the result is the same bit for bit.
+ * The number of launches has the parity of `steps`, so the final state is in
+ * buf1 exactly when `steps` is odd, whatever kernels run and on whatever
+ * device.
  *   buf0     [extent][C], the level's state on entry.
  *   buf1     [extent][C], scratch of the same size; must not overlap buf0.
  *   weights  host pointer to one octnca_level_weights (device arrays).
@@ -252,7 +254,9 @@ int octree_nca_infer(const octnca_model *model, const void *image, octnca_extent
 
 /* Step-kernel launches that octree_nca_infer enqueues for each level with the
  * model's step kernel (a measurement aid: the launches of a level add up to
- * its steps, one or two steps per launch).  The count depends only on the
+ * its steps, one or two steps per launch; a launch that runs several steps of
+ * a small 2D level counts one per step, as the single-step launches it stands
+ * for).  The count depends only on the
  * arguments, not on the device.
  *   launches  host, [L], written: launches[l] for level l (index 0 = finest).
  * Host only: enqueues nothing.  Errors: EINVAL (null pointer, a negative

@@ -153,6 +153,7 @@ StepArgs step_args(const octnca_model *m, const octnca_extent &e, const octnca_l
 
 // Launches that run steps t0 .. t1-1 of a level: one per step, or one per two
 // steps where the two-step kernel applies (a trailing odd step runs alone).
+// (Small 2D levels are planned by step_block_plan instead.)
 int32_t level_launches(const StepArgs &a, int32_t t0, int32_t t1) {
     if (t1 <= t0) return 0;
     return step_pairs(a) ? (t1 - t0 + 1) / 2 : t1 - t0;
@@ -197,6 +198,27 @@ int run_steps(const octnca_model *m, void *b0, void *b1, const octnca_extent &e,
             t += 1;
         }
         if (err != hipSuccess) return OCTNCA_EHIP;
+    }
+    return OCTNCA_OK;
+}
+
+// Enqueue steps 0 .. steps-1 of a small 2D level as `plan` divides them over
+// launches; launch k reads bufs[k % 2] and writes bufs[(k + 1) % 2], the first
+// one with its state formed as `in` says (src: the coarse state, null for a
+// seed).  seg: readout of the last state, or null.
+int run_block_steps(StepArgs a, const StepBlockPlan &plan, const void *src, void *b0, void *b1,
+                    StepBlockInput in, int32_t steps, uint8_t *seg, hipStream_t stream) {
+    void *bufs[2] = {b0, b1};
+    uint32_t t = 0;
+    for (int i = 0; i < plan.launches; ++i) {
+        const int n = plan.steps_of(i, steps);
+        a.step = t;
+        a.seg = i + 1 == plan.launches ? seg : nullptr;
+        if (launch_step_block(a, false, plan.tile, n, i == 0 ? src : bufs[i & 1],
+                              bufs[(i + 1) & 1], in, stream) != hipSuccess)
+            return OCTNCA_EHIP;
+        in.img = nullptr;   // the later launches read a state of the level
+        t += (uint32_t)n;
     }
     return OCTNCA_OK;
 }
@@ -305,9 +327,20 @@ int octree_nca_run_level(const octnca_model *model, void *buf0, void *buf1, octn
     const size_t bytes =
         (size_t)(extent.d * extent.h * extent.w) * model->channels * elem_bytes(model);
     if (overlap(buf0, bytes, buf1, bytes)) return OCTNCA_EINVAL;
-    // An even number of two-step launches (the rest one step each) keeps the
-    // number of launches of the same parity as `steps`: the result is in buf1
-    // exactly when steps is odd, whichever kernels run.
+    // The number of launches has the parity of `steps`, so that the result is
+    // in buf1 exactly when steps is odd, whichever kernels run: an even number
+    // of two-step launches (the rest one step each), or on small levels one
+    // launch more where the division over launches has the other parity.
+    const StepArgs a = step_args(model, extent, weights, level, seed, threshold, 0);
+    StepBlockPlan blocks;
+    if (step_block_plan(a, false, steps, 1, &blocks)) {
+        blocks.launches += (blocks.launches ^ steps) & 1;
+        st = run_block_steps(a, blocks, buf0, buf0, buf1, StepBlockInput{}, steps, nullptr,
+                             (hipStream_t)stream);
+        if (st) return st;
+        if (result_in_buf1) *result_in_buf1 = steps & 1;
+        return OCTNCA_OK;
+    }
     st = run_steps(model, buf0, buf1, extent, weights, level, 0, steps, seed, threshold,
                    (hipStream_t)stream, 0, nullptr, steps / 4 * 2);
     if (st) return st;
@@ -430,11 +463,20 @@ int infer_impl(const octnca_model *model, const void *image, octnca_extent fines
     const Dtype dt = dtype_of(model);
     // Levels whose first step reads the next coarser state directly (upsample
     // + inject fused into the step): that transition flips no buffer.
-    // Buffer flips: one per unfused upsample and one per step launch.
+    // Buffer flips: one per unfused upsample and one per step launch.  Small
+    // levels run several steps per launch, the first fused with the upsample
+    // or, on the coarsest level, with the seed.
     bool fused[kMaxLevels] = {};
+    bool block[kMaxLevels] = {};
+    StepBlockPlan blocks[kMaxLevels];
     int64_t flips = 0;
     for (int l = 0; l < levels; ++l) {
         const StepArgs a = step_args(model, p.ext[l], &weights[l], l, seed, threshold, batch);
+        block[l] = step_block_plan(a, false, steps[l], 1, &blocks[l]);
+        if (block[l]) {
+            flips += blocks[l].launches;
+            continue;
+        }
         if (l + 1 < levels && steps[l] >= 1) fused[l] = step_fuses_upsample(a);
         const int32_t t0 = fused_up_steps(a, fused[l], steps[l]);
         flips += (l + 1 < levels ? 1 : 0) + level_launches(a, t0, steps[l]);
@@ -446,13 +488,14 @@ int infer_impl(const octnca_model *model, const void *image, octnca_extent fines
             return OCTNCA_EHIP;
     }
     int cur = (int)(flips & 1);
-    if (launch_upsample(dt, nullptr, ext3(p.ext[levels - 1]), 1, 1, 1, img[levels - 1], bufs[cur],
+    if (!block[levels - 1] &&
+        launch_upsample(dt, nullptr, ext3(p.ext[levels - 1]), 1, 1, 1, img[levels - 1], bufs[cur],
                         model->n_in, model->channels, s) != hipSuccess)
         return OCTNCA_EHIP;
     bool seg_fused = false;
     for (int l = levels - 1; l >= 0; --l) {
         const int32_t *f = factors + 3 * l;
-        if (l < levels - 1 && !fused[l]) {
+        if (l < levels - 1 && !fused[l] && !block[l]) {
             if (launch_upsample(dt, bufs[cur], ext3(p.ext[l]), f[0], f[1], f[2], img[l],
                                 bufs[cur ^ 1], model->n_in, model->channels, s) != hipSuccess)
                 return OCTNCA_EHIP;
@@ -461,6 +504,25 @@ int infer_impl(const octnca_model *model, const void *image, octnca_extent fines
         if (level_events && level_events[2 * l] &&
             hipEventRecord((hipEvent_t)level_events[2 * l], s) != hipSuccess)
             return OCTNCA_EHIP;
+        if (block[l]) {
+            const StepArgs a = step_args(model, p.ext[l], &weights[l], l, seed, threshold, batch);
+            StepBlockInput in;
+            in.img = img[l];
+            if (l < levels - 1) {
+                in.coarse_w = (int)p.ext[l + 1].w;
+                in.fy = f[1];
+                in.fx = f[2];
+            }
+            seg_fused = l == 0 && seg != nullptr;
+            st = run_block_steps(a, blocks[l], l < levels - 1 ? bufs[cur] : nullptr, bufs[cur],
+                                 bufs[cur ^ 1], in, steps[l], l == 0 ? seg : nullptr, s);
+            if (st) return st;
+            cur ^= blocks[l].launches & 1;
+            if (level_events && level_events[2 * l + 1] &&
+                hipEventRecord((hipEvent_t)level_events[2 * l + 1], s) != hipSuccess)
+                return OCTNCA_EHIP;
+            continue;
+        }
         // The finest level's last launch writes the readout too when it is a
         // two-step launch; otherwise the readout kernel runs at the end.
         uint8_t *seg_last = nullptr;
@@ -838,6 +900,18 @@ int octree_nca_train_step(const octnca_model *model, const void *image, octnca_e
                                   tape(l, 0), model->n_in, model->channels, s);
         if (!ok(e)) return OCTNCA_EHIP;
         StepArgs a = step_args(model, p.ext[l], &weights[l], l, seed, threshold, 0);
+        StepBlockPlan blocks;
+        if (step_block_plan(a, true, steps[l], 1, &blocks)) {
+            for (int i = 0, t = 0; i < blocks.launches; ++i) {
+                const int n = blocks.steps_of(i, steps[l]);
+                a.step = (uint32_t)t;
+                if (!ok(launch_step_block(a, true, blocks.tile, n, tape(l, t), tape(l, t + 1),
+                                          StepBlockInput{}, s)))
+                    return OCTNCA_EHIP;
+                t += n;
+            }
+            continue;
+        }
         for (int t = 0; t < steps[l]; ++t) {
             a.step = (uint32_t)t;
             if (!ok(train_forward_step(a, tape(l, t), tape(l, t + 1), s))) return OCTNCA_EHIP;

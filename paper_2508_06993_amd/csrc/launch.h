@@ -93,6 +93,33 @@ hipError_t launch_step_pair(const StepArgs &a, const void *src, void *dst, hipSt
 hipError_t launch_step_pair_up(const StepArgs &a, const void *coarse, int coarse_w, int fz,
                                int fy, int fx, const void *img, void *dst, hipStream_t stream);
 
+// Several steps of a small 2D level in one launch (step_block.hip).
+// step_block_plan: whether a run of `steps` steps (of `images` images at once)
+// takes these launches, and how: `launches` of them, launch i running
+// steps / launches steps, one more for i < steps % launches, on tiles of
+// `tile` x `tile` cells.  tape: the training forward (split-bf16 operands).
+struct StepBlockPlan {
+    int tile = 0;
+    int launches = 0;
+    int steps_of(int i, int steps) const { return steps / launches + (i < steps % launches); }
+};
+bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBlockPlan *plan);
+// Where a launch's first state comes from: img null, a state of the level at
+// src; else the coarse state at src (width coarse_w, factors fy, fx) with the
+// level's image, or with src null the image and zero hidden channels.
+// Strides (elements) between the images of a batch.
+struct StepBlockInput {
+    const void *img = nullptr;
+    int coarse_w = 0, fy = 1, fx = 1;
+    int images = 1;
+    int64_t src_stride = 0, dst_stride = 0, img_stride = 0;
+};
+// Steps a.step .. a.step + steps - 1; dst receives the last state, or with
+// `tape` the state after step a.step + s at dst + s states.  a.seg: readout of
+// the last state, or null.
+hipError_t launch_step_block(const StepArgs &a, bool tape, int tile, int steps, const void *src,
+                             void *dst, StepBlockInput in, hipStream_t stream);
+
 // Training (fp32 states): backward of one step (state `src` before the step,
 // gout = dL/dS'), writing gin = dL/dS (may alias gout) and adding the weight
 // gradients to g; ws holds step_backward_workspace_floats floats.
