@@ -21,6 +21,7 @@ namespace {
 constexpr int64_t kMaxDim = int64_t(1) << 30;      // per axis (kernels index with int)
 constexpr int64_t kMaxCells = int64_t(1) << 36;    // per level
 constexpr int kMaxLevels = 16;
+constexpr int kMaxGroup = 64;   // images of a batch that run together at most
 constexpr size_t kAlign = 256;
 
 size_t align_up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
@@ -218,6 +219,7 @@ int run_block_steps(StepArgs a, const StepBlockPlan &plan, const void *src, void
                               bufs[(i + 1) & 1], in, stream) != hipSuccess)
             return OCTNCA_EHIP;
         in.img = nullptr;   // the later launches read a state of the level
+        in.src_stride = in.dst_stride;
         t += (uint32_t)n;
     }
     return OCTNCA_OK;
@@ -422,11 +424,19 @@ int octree_nca_infer_launches(const octnca_model *model, octnca_extent finest, i
 
 namespace {
 
+// An inference whose levels above `level` have run already: it starts with the
+// upsample from `coarse`, the state of level `level` + 1.
+struct Resume {
+    int32_t level;
+    const void *coarse;
+};
+
 int infer_impl(const octnca_model *model, const void *image, octnca_extent finest,
                int32_t levels, const int32_t *factors, const octnca_level_weights *weights,
                const int32_t *steps, float fire_rate, uint64_t seed, void *workspace,
                size_t workspace_bytes, void *final_state, uint8_t *seg,
-               void *const *level_events, void *stream, uint32_t batch, bool check_only) {
+               void *const *level_events, void *stream, uint32_t batch, bool check_only,
+               const Resume *resume = nullptr) {
     Plan p;
     int st = make_plan(model, finest, levels, factors, final_state != nullptr, &p);
     if (st) return st;
@@ -470,7 +480,8 @@ int infer_impl(const octnca_model *model, const void *image, octnca_extent fines
     bool block[kMaxLevels] = {};
     StepBlockPlan blocks[kMaxLevels];
     int64_t flips = 0;
-    for (int l = 0; l < levels; ++l) {
+    const int32_t top = resume ? resume->level : levels - 1;   // first level to run
+    for (int l = 0; l <= top; ++l) {
         const StepArgs a = step_args(model, p.ext[l], &weights[l], l, seed, threshold, batch);
         block[l] = step_block_plan(a, false, steps[l], 1, &blocks[l]);
         if (block[l]) {
@@ -481,22 +492,33 @@ int infer_impl(const octnca_model *model, const void *image, octnca_extent fines
         const int32_t t0 = fused_up_steps(a, fused[l], steps[l]);
         flips += (l + 1 < levels ? 1 : 0) + level_launches(a, t0, steps[l]);
     }
-    for (int l = 1; l < levels; ++l) {
+    for (int l = 1; l <= top; ++l) {
         const int32_t *f = factors + 3 * (l - 1);
         if (launch_pool(dt, img[l - 1], ext3(p.ext[l]), (void *)img[l], f[0], f[1], f[2],
                         model->n_in, s) != hipSuccess)
             return OCTNCA_EHIP;
     }
     int cur = (int)(flips & 1);
-    if (!block[levels - 1] &&
+    // the state that level l + 1 left, read by level l's upsample
+    const void *coarse = resume ? resume->coarse : bufs[cur];
+    if (resume && cur == 1 && overlap(coarse, 1, final_state, state_bytes)) {
+        // the first launch writes the buffer that holds the coarse state: move that
+        const octnca_extent &e = p.ext[top + 1];
+        if (hipMemcpyAsync(bufs[1], coarse, (size_t)(e.d * e.h * e.w) * model->channels * eb,
+                           hipMemcpyDeviceToDevice, s) != hipSuccess)
+            return OCTNCA_EHIP;
+        coarse = bufs[1];
+    }
+    if (!resume && !block[levels - 1] &&
         launch_upsample(dt, nullptr, ext3(p.ext[levels - 1]), 1, 1, 1, img[levels - 1], bufs[cur],
                         model->n_in, model->channels, s) != hipSuccess)
         return OCTNCA_EHIP;
     bool seg_fused = false;
-    for (int l = levels - 1; l >= 0; --l) {
+    for (int l = top; l >= 0; --l) {
         const int32_t *f = factors + 3 * l;
+        if (l != top || !resume) coarse = bufs[cur];
         if (l < levels - 1 && !fused[l] && !block[l]) {
-            if (launch_upsample(dt, bufs[cur], ext3(p.ext[l]), f[0], f[1], f[2], img[l],
+            if (launch_upsample(dt, coarse, ext3(p.ext[l]), f[0], f[1], f[2], img[l],
                                 bufs[cur ^ 1], model->n_in, model->channels, s) != hipSuccess)
                 return OCTNCA_EHIP;
             cur ^= 1;
@@ -514,7 +536,7 @@ int infer_impl(const octnca_model *model, const void *image, octnca_extent fines
                 in.fx = f[2];
             }
             seg_fused = l == 0 && seg != nullptr;
-            st = run_block_steps(a, blocks[l], l < levels - 1 ? bufs[cur] : nullptr, bufs[cur],
+            st = run_block_steps(a, blocks[l], l < levels - 1 ? coarse : nullptr, bufs[cur],
                                  bufs[cur ^ 1], in, steps[l], l == 0 ? seg : nullptr, s);
             if (st) return st;
             cur ^= blocks[l].launches & 1;
@@ -540,15 +562,15 @@ int infer_impl(const octnca_model *model, const void *image, octnca_extent fines
         }
         int32_t t0 = 0;
         if (fused[l]) {
-            // step 0 (or steps 0 and 1) from the coarse state bufs[cur] (level
-            // l + 1) and image l
+            // step 0 (or steps 0 and 1) from the coarse state (level l + 1)
+            // and image l
             StepArgs a = step_args(model, p.ext[l], &weights[l], l, seed, threshold, batch);
             t0 = fused_up_steps(a, true, steps[l]);
             if (t0 == steps[l]) a.seg = seg_last;   // this launch is the level's last
             const hipError_t err =
-                t0 == 2 ? launch_step_pair_up(a, bufs[cur], (int)p.ext[l + 1].w, f[0], f[1], f[2],
+                t0 == 2 ? launch_step_pair_up(a, coarse, (int)p.ext[l + 1].w, f[0], f[1], f[2],
                                               img[l], bufs[cur ^ 1], s)
-                        : launch_step_up(a, bufs[cur], (int)p.ext[l + 1].h, (int)p.ext[l + 1].w,
+                        : launch_step_up(a, coarse, (int)p.ext[l + 1].h, (int)p.ext[l + 1].w,
                                          f[0], f[1], f[2], img[l], bufs[cur ^ 1], s);
             if (err != hipSuccess) return OCTNCA_EHIP;
             cur ^= 1;
@@ -591,6 +613,163 @@ int octree_nca_infer(const octnca_model *model, const void *image, octnca_extent
 }  // extern "C"
 
 namespace {
+
+// A batch is run in groups.  The small levels of one image leave most of the
+// chip idle, so the coarse levels of a group's images run in the same launches,
+// with their level states in the group's own final states, which hold nothing
+// yet.  Images of a group: as many as have room for their pyramid images in the
+// workspace, the batch divided evenly; 1 where the groups would not apply.
+int32_t batch_group(const octnca_model *m, const Plan &p, int32_t batch, int32_t levels,
+                    size_t workspace_bytes, bool with_final_states) {
+    if (batch < 2 || m->ndim != 2 || !with_final_states) return 1;
+    const size_t eb = elem_bytes(m);
+    size_t pyramid = 0;   // n images' levels need at most n times this
+    for (int l = 1; l < levels; ++l)
+        pyramid += align_up((size_t)(p.ext[l].h * p.ext[l].w) * m->n_in * eb);
+    int64_t n = std::min<int64_t>(batch, kMaxGroup);
+    if (pyramid > 0) n = std::min<int64_t>(n, (int64_t)(workspace_bytes / pyramid));
+    if (n < 2) return 1;
+    const int64_t groups = (batch + n - 1) / n;
+    return (int32_t)((batch + groups - 1) / groups);
+}
+
+// The finest level from which a group of n images runs together up to the
+// coarsest one (levels: none does).  The levels are those that the multi-step
+// launches take; two buffers of the finest of them, or of level 1 where level
+// 0 is among them, have to fit the final states.
+int32_t group_levels(const octnca_model *m, const Plan &p, int32_t n, int32_t levels,
+                     const octnca_level_weights *weights, const int32_t *steps) {
+    int32_t from = levels;
+    StepBlockPlan blocks;
+    while (from > 0 &&
+           step_block_plan(step_args(m, p.ext[from - 1], &weights[from - 1], from - 1, 0, 0, 0),
+                           false, steps[from - 1], n, &blocks))
+        --from;
+    const int64_t cells = p.ext[0].h * p.ext[0].w;
+    auto fits = [&](int l) { return 2 * p.ext[l].h * p.ext[l].w <= cells; };
+    if (from == 0 && levels > 1 && !fits(1)) from = 1;
+    while (from > 0 && from < levels && !fits(from)) ++from;
+    return from;
+}
+
+// A group of n images (their first one is image `batch` of the call): levels
+// from `together` up run for all images at once, the finer ones image by image
+// (the finest, where it runs together, in as large parts as leave a second
+// buffer).  The arguments have been checked.
+int infer_group(const octnca_model *model, const void *images, int32_t n, octnca_extent finest,
+                int32_t levels, const int32_t *factors, const octnca_level_weights *weights,
+                const int32_t *steps, float fire_rate, uint64_t seed, void *workspace,
+                size_t workspace_bytes, void *final_states, uint8_t *segs, void *stream,
+                uint32_t batch, int32_t together) {
+    Plan p;
+    int st = make_plan(model, finest, levels, factors, true, &p);
+    if (st) return st;
+    uint64_t threshold;
+    if (!fire_threshold(fire_rate, &threshold)) return OCTNCA_EINVAL;
+    const hipStream_t s = (hipStream_t)stream;
+    const Dtype dt = dtype_of(model);
+    const size_t eb = elem_bytes(model);
+    const int64_t c = model->channels;
+    auto cells_of = [&](int l) { return p.ext[l].h * p.ext[l].w; };
+    const size_t state_bytes = (size_t)(cells_of(0) * c) * eb;
+    const size_t image_bytes = (size_t)(cells_of(0) * model->n_in) * eb;
+    char *const out = (char *)final_states;
+
+    // Pyramids of the group, [n][h][w] per level: the batch as a z axis.  Only
+    // the levels that run together need them.
+    const int32_t shared = std::max(together, 1);   // finest level of the shared coarse part
+    const void *img[kMaxLevels];
+    img[0] = images;
+    size_t off = 0;
+    for (int l = 1; l < levels; ++l) {
+        const int32_t *f = factors + 3 * (l - 1);
+        void *dst = (char *)workspace + off;
+        const Extent3 e{n, p.ext[l].h, p.ext[l].w};
+        if (launch_pool(dt, img[l - 1], e, dst, f[0], f[1], f[2], model->n_in, s) != hipSuccess)
+            return OCTNCA_EHIP;
+        img[l] = dst;
+        off += align_up((size_t)(n * cells_of(l) * model->n_in) * eb);
+    }
+
+    // Coarse levels of all images: two buffers at the end of the group's final
+    // states, image i's state of a level at i states of that level.  The last
+    // level's result lands in the one at the very end.
+    const void *coarse = nullptr;
+    const size_t shared_bytes = shared < levels ? (size_t)(cells_of(shared) * c) * eb : 0;
+    if (shared < levels) {
+        void *bufs[2] = {out + n * (state_bytes - shared_bytes),
+                         out + n * (state_bytes - 2 * shared_bytes)};
+        StepBlockPlan blocks[kMaxLevels];
+        int flips = 0;
+        for (int l = shared; l < levels; ++l) {
+            const StepArgs a = step_args(model, p.ext[l], &weights[l], l, seed, threshold, batch);
+            if (!step_block_plan(a, false, steps[l], n, &blocks[l])) return OCTNCA_EINVAL;
+            flips += blocks[l].launches;
+        }
+        int cur = flips & 1;
+        for (int l = levels - 1; l >= shared; --l) {
+            const StepArgs a = step_args(model, p.ext[l], &weights[l], l, seed, threshold, batch);
+            StepBlockInput in;
+            in.images = n;
+            in.img = img[l];
+            in.img_stride = cells_of(l) * model->n_in;
+            in.dst_stride = cells_of(l) * c;
+            if (l < levels - 1) {
+                in.coarse_w = (int)p.ext[l + 1].w;
+                in.fy = factors[3 * l + 1];
+                in.fx = factors[3 * l + 2];
+                in.src_stride = cells_of(l + 1) * c;
+            }
+            st = run_block_steps(a, blocks[l], l < levels - 1 ? bufs[cur] : nullptr, bufs[cur],
+                                 bufs[cur ^ 1], in, steps[l], nullptr, s);
+            if (st) return st;
+            cur ^= blocks[l].launches & 1;
+        }
+        coarse = bufs[0];
+    }
+
+    for (int32_t b = 0; b < n;) {
+        // Images b .. b + k - 1: their final states and as many further ones as
+        // a second buffer, short of the coarse states still to be read.
+        const int64_t left = n - b;
+        int32_t k = 1;
+        StepBlockPlan blocks;
+        StepArgs a = step_args(model, p.ext[0], &weights[0], 0, seed, threshold, batch + b);
+        if (together == 0)
+            k = (int32_t)std::max<int64_t>(
+                1, left * (int64_t)(state_bytes - shared_bytes) / (int64_t)(2 * state_bytes));
+        const void *from =
+            coarse ? (const void *)((const char *)coarse + b * shared_bytes) : nullptr;
+        const void *image = (const char *)images + b * image_bytes;
+        uint8_t *seg = segs ? segs + b * cells_of(0) : nullptr;
+        if (k > 1 && step_block_plan(a, false, steps[0], k, &blocks)) {
+            StepBlockInput in;
+            in.images = k;
+            in.img = image;
+            in.img_stride = cells_of(0) * model->n_in;
+            in.dst_stride = cells_of(0) * c;
+            if (from) {
+                in.coarse_w = (int)p.ext[1].w;
+                in.fy = factors[1];
+                in.fx = factors[2];
+                in.src_stride = cells_of(1) * c;
+            }
+            void *mine = out + b * state_bytes, *other = out + (b + k) * state_bytes;
+            const bool odd = blocks.launches & 1;
+            st = run_block_steps(a, blocks, from, odd ? other : mine, odd ? mine : other, in,
+                                 steps[0], seg, s);
+        } else {
+            k = 1;
+            const Resume resume{shared - 1, from};
+            st = infer_impl(model, image, finest, levels, factors, weights, steps, fire_rate, seed,
+                            workspace, workspace_bytes, out + b * state_bytes, seg, nullptr,
+                            stream, batch + (uint32_t)b, false, from ? &resume : nullptr);
+        }
+        if (st) return st;
+        b += k;
+    }
+    return OCTNCA_OK;
+}
 
 // Static scratch of octree_nca_infer_static: the pyramid images and the second
 // state buffer of one inference.  Each device the library runs on holds its
@@ -683,10 +862,24 @@ int octree_nca_infer_batch(const octnca_model *model, const void *images, int32_
                         (uint32_t)b, true);
         if (st) return st;
     }
-    for (int32_t b = 0; b < batch; ++b) {
-        st = infer_impl(model, image_of(b), finest, levels, factors, weights, steps, fire_rate,
-                        seed, workspace, workspace_bytes, state_of(b), seg_of(b), nullptr, stream,
-                        (uint32_t)b, false);
+    // groups of images whose coarse levels run together, the others one by one
+    Plan p;
+    if ((st = make_plan(model, finest, levels, factors, final_states != nullptr, &p))) return st;
+    const int32_t group = batch_group(model, p, batch, levels, workspace_bytes,
+                                      final_states != nullptr);
+    for (int32_t b = 0, n; b < batch; b += n) {
+        n = std::min(group, batch - b);
+        const int32_t together = n > 1 ? group_levels(model, p, n, levels, weights, steps) : levels;
+        if (together < levels) {
+            st = infer_group(model, image_of(b), n, finest, levels, factors, weights, steps,
+                             fire_rate, seed, workspace, workspace_bytes, state_of(b), seg_of(b),
+                             stream, (uint32_t)b, together);
+        } else {
+            n = 1;
+            st = infer_impl(model, image_of(b), finest, levels, factors, weights, steps, fire_rate,
+                            seed, workspace, workspace_bytes, state_of(b), seg_of(b), nullptr,
+                            stream, (uint32_t)b, false);
+        }
         if (st) return st;
     }
     return OCTNCA_OK;

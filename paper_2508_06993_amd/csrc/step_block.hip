@@ -450,7 +450,8 @@ bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBl
     // One launch per step on the row kernel, measured: 5.0 us up to 128^2
     // cells, 6.8 at 256^2, 8.8 at 320^2, 11.3 at 512^2, 20.6 at 724^2, 27.7 at
     // 1024^2 (the training forward about 1 us more).
-    double best = steps * ((tape ? 5.5 : 4.5) + (double)(h * w * images) / 45000.0);
+    // The images of a batch would run one after another there.
+    double best = (double)steps * images * ((tape ? 5.5 : 4.5) + (double)(h * w) / 45000.0);
     bool use = false;
     for (int tile : {4, 6, 8, 10, 12, 14, 16, 18, 20, 22, 24, 28}) {
         if (tile > 4 && tile / 2 >= std::max(h, w)) break;
