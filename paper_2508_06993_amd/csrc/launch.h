@@ -137,6 +137,27 @@ size_t level_backward_workspace_floats(int ndim, int channels, int hidden, Exten
 hipError_t launch_level_backward(const StepArgs &a, int32_t steps, const float *states,
                                  const float *gout, float *gin, LevelGradsDev g, float *ws,
                                  hipStream_t stream);
+// The backward's per-cell part on large tiles (bwd_block.hip; C = 16, H = 64):
+// whether it runs a level of `steps` steps, and how: `launches` launches,
+// launch i running steps / launches steps, one more for i < steps % launches,
+// on tiles of `tile` x `tile` cells (2D; 4 x 8 x 8 and one step in 3D), each
+// block with a row of weight-gradient sums (bwd_block_rows of them, at most
+// max_blocks).
+struct BwdBlockPlan {
+    int tile = 0;
+    int launches = 0;
+    int steps_of(int i, int steps) const { return steps / launches + (i < steps % launches); }
+};
+bool bwd_block_plan(const StepArgs &a, int steps, int64_t max_blocks, BwdBlockPlan *plan);
+int64_t bwd_block_rows(const StepArgs &a, const BwdBlockPlan &plan);
+// Backward of steps a.step, a.step - 1, .. (steps of them): state is the state
+// before step a.step, the earlier ones lie one state of the level before it
+// each.  G' = gout + conv^T(gp_prev) (gp_prev null: gout); gpart and gp
+// receive G' + gS and gP of the last of these steps, both [cells][C].
+hipError_t launch_bwd_block(const StepArgs &a, const BwdBlockPlan &plan, int steps,
+                            const float *state, const float *gout, const float *gp_prev,
+                            float *gpart, float *gp, float *partial, bool accumulate,
+                            hipStream_t stream);
 // Adjoint of the upsample + inject from `coarse` (extent of the coarse level).
 hipError_t launch_upsample_adjoint(const float *gfine, Extent3 coarse, int fz, int fy, int fx,
                                    int n_in, int channels, float *gcoarse, hipStream_t stream);

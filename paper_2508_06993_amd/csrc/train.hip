@@ -25,6 +25,8 @@
 // step runs bwd_cell once per step, each after the first forming its G' from
 // the previous one's (G' + gS, gP) with the transposed convolution fused and
 // adding to its block's partial row, then bwd_conv_t and wgrad_reduce once.
+// C = 16, H = 64 takes the larger tiles of bwd_block.hip for the first kernel
+// (several steps per launch in 2D) wherever bwd_block_plan says so.
 #include "launch.h"
 
 namespace octnca {
@@ -718,7 +720,8 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_cell_mfma(
     }
 }
 
-template <int NDIM, int C, int H>
+// CELL_MAJOR: gp is [cells][C] (bwd_block), else [C][cells].
+template <int NDIM, int C, int H, bool CELL_MAJOR>
 __global__ __launch_bounds__(kBwdThreads) void bwd_conv_t(
     const float *__restrict__ gpart, const float *__restrict__ gp, int dd, int dh, int dw,
     int tiles_x, int tiles_y, const float *__restrict__ conv_w, float *__restrict__ gin,
@@ -737,16 +740,19 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_conv_t(
     const int x0 = bx * T::TX, y0 = by * T::TY, z0 = bz * T::TZ;
     stage<NCELL * C, 8>(
         [&](int i) {
-            const int c = i / NCELL, cell = i % NCELL;
+            const int c = CELL_MAJOR ? i % C : i / NCELL, cell = CELL_MAJOR ? i / C : i % NCELL;
             const int lx = cell % HX, ly = (cell / HX) % HY, lz = cell / (HX * HY);
             const int gx = x0 + lx - 1, gy = y0 + ly - 1, gz = NDIM == 3 ? z0 + lz - 1 : 0;
             const bool in = gx >= 0 && gx < dw && gy >= 0 && gy < dh && gz >= 0 && gz < dd;
             const int cx = min(max(gx, 0), dw - 1), cy = min(max(gy, 0), dh - 1),
                       cz = min(max(gz, 0), dd - 1);
-            const float v = gp[c * cells + ((int64_t)cz * dh + cy) * dw + cx];
+            const int64_t p = ((int64_t)cz * dh + cy) * dw + cx;
+            const float v = gp[CELL_MAJOR ? p * C + c : c * cells + p];
             return in ? v : 0.f;
         },
-        [&](int i, float v) { tile[i / NCELL][i % NCELL] = v; });
+        [&](int i, float v) {
+            tile[CELL_MAJOR ? i % C : i / NCELL][CELL_MAJOR ? i / C : i % NCELL] = v;
+        });
     __syncthreads();
 
     const int tx = threadIdx.x % T::TX, ty = (threadIdx.x / T::TX) % T::TY,
@@ -837,14 +843,15 @@ void enqueue_bwd_cell(const StepArgs &a, const BwdGrid<NDIM> &gr, const float *s
 
 template <int NDIM, int C, int H>
 void enqueue_tail(const StepArgs &a, const BwdGrid<NDIM> &gr, const float *gpart, const float *gp,
-                  float *gin, const float *partial, LevelGradsDev g, bool overwrite,
-                  hipStream_t stream) {
+                  float *gin, const float *partial, int64_t rows, bool cell_major, LevelGradsDev g,
+                  bool overwrite, hipStream_t stream) {
     constexpr int TAPS = NDIM == 3 ? 27 : 9;
-    bwd_conv_t<NDIM, C, H><<<(unsigned)gr.blocks, kBwdThreads, 0, stream>>>(
+    auto conv_t = cell_major ? bwd_conv_t<NDIM, C, H, true> : bwd_conv_t<NDIM, C, H, false>;
+    conv_t<<<(unsigned)gr.blocks, kBwdThreads, 0, stream>>>(
         gpart, gp, (int)a.ext.d, (int)a.ext.h, (int)a.ext.w, gr.tiles_x, gr.tiles_y, a.w.conv_w,
         gin, a.ext.cells());
     wgrad_reduce<C, H, TAPS><<<(WG<C, H, TAPS>::N + 63) / 64, 64 * kRedWaves, 0, stream>>>(
-        partial, gr.cblocks, g, overwrite ? 1 : 0);
+        partial, rows, g, overwrite ? 1 : 0);
 }
 
 // One step: bwd_cell, bwd_conv_t, wgrad_reduce.
@@ -857,9 +864,18 @@ hipError_t launch_bwd(const StepArgs &a, const float *src, const float *gout, fl
     float *gpart = ws;                 // G' + gS
     float *gp = gpart + cells * C;     // gP, [C][cells]
     float *partial = gp + cells * C;   // [cblocks][entries]
+    BwdBlockPlan plan;
+    if (bwd_block_plan(a, 1, gr.cblocks, &plan)) {
+        const hipError_t e = launch_bwd_block(a, plan, 1, src, gout, nullptr, gpart, gp, partial,
+                                              false, stream);
+        if (e != hipSuccess) return e;
+        enqueue_tail<NDIM, C, H>(a, gr, gpart, gp, gin, partial, bwd_block_rows(a, plan), true, g,
+                                 false, stream);
+        return hipGetLastError();
+    }
     enqueue_bwd_cell<NDIM, NIN, C, H>(a, gr, src, gout, nullptr, gpart, gp, partial, false,
                                       stream);
-    enqueue_tail<NDIM, C, H>(a, gr, gpart, gp, gin, partial, g, false, stream);
+    enqueue_tail<NDIM, C, H>(a, gr, gpart, gp, gin, partial, gr.cblocks, false, g, false, stream);
     return hipGetLastError();
 }
 
@@ -879,6 +895,23 @@ hipError_t launch_bwd_level(const StepArgs &a0, int32_t steps, const float *stat
     float *partial = ws + 4 * cells * C;
     StepArgs a = a0;
     int cur = 0;
+    BwdBlockPlan plan;
+    if (bwd_block_plan(a, steps, gr.cblocks, &plan)) {
+        int32_t t = steps - 1;
+        for (int i = 0; i < plan.launches; ++i) {
+            const int n = plan.steps_of(i, steps);
+            a.step = (uint32_t)t;
+            const hipError_t e = launch_bwd_block(
+                a, plan, n, states + (size_t)t * cells * C, i == 0 ? gout : gpart[cur ^ 1],
+                i == 0 ? nullptr : gp[cur ^ 1], gpart[cur], gp[cur], partial, i > 0, stream);
+            if (e != hipSuccess) return e;
+            cur ^= 1;
+            t -= n;
+        }
+        enqueue_tail<NDIM, C, H>(a, gr, gpart[cur ^ 1], gp[cur ^ 1], gin, partial,
+                                 bwd_block_rows(a, plan), true, g, true, stream);
+        return hipGetLastError();
+    }
     for (int32_t t = steps - 1; t >= 0; --t) {
         a.step = (uint32_t)t;
         const bool first = t == steps - 1;
@@ -888,7 +921,8 @@ hipError_t launch_bwd_level(const StepArgs &a0, int32_t steps, const float *stat
                                           partial, !first, stream);
         cur ^= 1;
     }
-    enqueue_tail<NDIM, C, H>(a, gr, gpart[cur ^ 1], gp[cur ^ 1], gin, partial, g, true, stream);
+    enqueue_tail<NDIM, C, H>(a, gr, gpart[cur ^ 1], gp[cur ^ 1], gin, partial, gr.cblocks, false, g,
+                             true, stream);
     return hipGetLastError();
 }
 
