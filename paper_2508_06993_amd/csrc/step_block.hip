@@ -66,13 +66,13 @@ enum class BlockIn : int {
 template <typename T, int NIN, class Mlp, BlockIn IN, bool TAPE>
 __global__ __launch_bounds__(kBlockThreads, 1) void nca_steps_block_2d(const BlockArgs A) {
     constexpr int C = Mlp::kChannels;
-    constexpr int NQ = CellChunks<T>::N;                 // 16-byte chunks of a 16-channel cell
+    using Ch = CellChunk<T, C>;
+    constexpr int NQ = Ch::N;
     constexpr int kCellBytes = C * (int)sizeof(T);
-    constexpr int kChunks = kCellBytes / 16;
+    constexpr int kChunks = Ch::kUsed;
     constexpr int kCellsPerLoad = 64 / NQ;               // cells a wave's load covers
     constexpr int kMaxLoads =
         (kRegionMax * kRegionMax + kCellsPerLoad * kBlockWaves - 1) / (kCellsPerLoad * kBlockWaves);
-    static_assert(kCellBytes % 16 == 0 && kChunks <= NQ, "whole 16-byte chunks");
     __shared__ float4 state[2][4 * kQuadPlane];
     __shared__ uint64_t fire[kBlockMaxSteps][kRegionMax];
 
@@ -113,9 +113,7 @@ __global__ __launch_bounds__(kBlockThreads, 1) void nca_steps_block_2d(const Blo
                                   (int)(((float)x + 0.5f) * (1.f / A.fx)));
             else
                 cell = (uint32_t)(y * A.dw + x);
-            const v4u t = __builtin_amdgcn_raw_buffer_load_b128(
-                r, ok ? cell * kCellBytes + (uint32_t)chunk * 16 : kOut, 0, 0);
-            v[j] = make_uint4(t[0], t[1], t[2], t[3]);
+            v[j] = Ch::load(r, ok ? cell * kCellBytes + (uint32_t)(chunk * Ch::kBytes) : kOut);
         }
     }
     // image values of the region's input channels (one cell per thread and turn)
@@ -201,18 +199,7 @@ __global__ __launch_bounds__(kBlockThreads, 1) void nca_steps_block_2d(const Blo
 #pragma unroll
         for (int j = 0; j < kMaxLoads; ++j) {
             const int e = (j * kBlockWaves + wave) * kCellsPerLoad + lane % kCellsPerLoad;
-            if (e < rcells) {
-                if constexpr (NQ == 4) {
-                    state[0][chunk * kQuadPlane + e] =
-                        make_float4(__uint_as_float(v[j].x), __uint_as_float(v[j].y),
-                                    __uint_as_float(v[j].z), __uint_as_float(v[j].w));
-                } else {
-                    float f[8];
-                    Storage<__half>::unpack(v[j], f);
-                    state[0][(2 * chunk) * kQuadPlane + e] = make_float4(f[0], f[1], f[2], f[3]);
-                    state[0][(2 * chunk + 1) * kQuadPlane + e] = make_float4(f[4], f[5], f[6], f[7]);
-                }
-            }
+            if (e < rcells) Ch::put(state[0], kQuadPlane, chunk, e, v[j]);
         }
         const int t = threadIdx.x;
 #pragma unroll
@@ -441,7 +428,7 @@ bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBl
         const bool mlp_ok = a.kc.mlp == MfmaMlp::Default ||
                             a.kc.mlp == (a.dtype == Dtype::F32 ? MfmaMlp::F16S : MfmaMlp::F16);
         if (!mlp_ok) return false;
-        if (!is_size(a, 16, 64) && !(is_size(a, 12, 48) && a.dtype == Dtype::F32)) return false;
+        if (!is_size(a, 16, 64) && !is_size(a, 12, 48)) return false;
     }
     // (the kernel's exact divisions need h, w < 2^19, its offsets 32 bits)
     const int64_t h = a.ext.h, w = a.ext.w;
@@ -513,6 +500,8 @@ hipError_t launch_step_block(const StepArgs &a, bool tape, int tile, int steps, 
     if (tape) {
         if (how != BlockIn::State) return hipErrorInvalidValue;
         launch_block_nin<float, MlpBf16x3, BlockIn::State, true>(b, a.n_in, grid, stream);
+    } else if (a.dtype == Dtype::F16 && is_size(a, 12, 48)) {
+        launch_block_in<__half, MlpF16M<12, 48>>(b, a.n_in, how, grid, stream);
     } else if (a.dtype == Dtype::F16) {
         launch_block_in<__half, MlpF16>(b, a.n_in, how, grid, stream);
     } else if (is_size(a, 12, 48)) {

@@ -234,19 +234,30 @@ struct MlpBf16x3 {
     }
 };
 
+// Feature order of a model with C channels (C <= 16, a multiple of 4): slot
+// s < 4 of lane group g is state channel 4g + s, slot s >= 4 perception
+// channel 4g + s - 4; lane groups g >= C / 4 hold no channel.
+template <int C>
+__device__ __forceinline__ int feature_of_c(int slot, int g) {
+    return slot < 4 ? 4 * g + slot : C + 4 * g + (slot - 4);
+}
+
 // fp16 operands, single pass (for fp16 state storage): weights, features and
 // hidden activations rounded to fp16, products accumulated in fp32 on
 // v_mfma_f32_16x16x32_f16; 4 + 2 MFMAs per 16 cells.
-struct MlpF16 {
-    static constexpr int kChannels = kC, kHidden = kH;
+template <int C, int H>
+struct MlpF16M {
+    static_assert(C % 4 == 0 && C <= kC && H % 16 == 0 && H <= kH, "fits the 16 / 64 lanes");
+    static constexpr int kChannels = C, kHidden = H;
+    static constexpr int NT = H / 16;   // hidden tiles computed (a smaller model: see MlpF16SM)
     static constexpr float kPerceptionScale = 1.f;
-    v8h w1[4];
-    v4f b1[4];
+    v8h w1[NT];
+    v4f b1[NT];
     v8h w2[2];
 
     __device__ __forceinline__ void pin_all() {
 #pragma unroll
-        for (int jt = 0; jt < 4; ++jt) {
+        for (int jt = 0; jt < NT; ++jt) {
             pin(w1[jt]);
             pin(b1[jt]);
         }
@@ -257,22 +268,30 @@ struct MlpF16 {
     __device__ __forceinline__ void load(const float *__restrict__ W1, const float *__restrict__ B1,
                                          const float *__restrict__ W2, int n, int g, int nin,
                                          int ld1 = 2 * kChannels, int ld2 = kHidden) {
+        const bool g_ok = g < C / 4;
+        const int gc = g_ok ? g : 0;
 #pragma unroll
-        for (int jt = 0; jt < 4; ++jt) {
+        for (int jt = 0; jt < NT; ++jt) {
             v8f x;
 #pragma unroll
-            for (int s = 0; s < 8; ++s) x[s] = W1[(jt * 16 + n) * ld1 + feature_of(s, g)];
+            for (int s = 0; s < 8; ++s) {
+                const float v = W1[(jt * 16 + n) * ld1 + feature_of_c<C>(s, gc)];
+                x[s] = g_ok ? v : 0.f;
+            }
             w1[jt] = __builtin_convertvector(x, v8h);
 #pragma unroll
             for (int i = 0; i < 4; ++i) b1[jt][i] = B1[jt * 16 + 4 * g + i];
         }
+        const bool row_ok = n >= nin && n < C;
+        const int nc = n < C ? n : 0;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             v8f x;
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
-                const float v = W2[n * ld2 + MlpBf16x3::hidden_of(p, s, g)];   // loaded for every n
-                x[s] = n < nin ? 0.f : v;
+                const int hid = MlpBf16x3::hidden_of(p, s, g);
+                const float v = W2[nc * ld2 + (hid < H ? hid : 0)];   // loaded for every n
+                x[s] = row_ok && hid < H ? v : 0.f;
             }
             w2[p] = __builtin_convertvector(x, v8h);
         }
@@ -288,13 +307,14 @@ struct MlpF16 {
     // features already in fp16 (slot s = feature_of(s, g))
     __device__ __forceinline__ void layer1_h(const v8h &fh, v4f acc[4]) const {
 #pragma unroll
-        for (int jt = 0; jt < 4; ++jt)
+        for (int jt = 0; jt < NT; ++jt)
             acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[jt], fh, b1[jt], 0, 0, 0);
     }
 
     // ReLU after the rounding to fp16, as packed fp16 max (half the
     // instructions of an fp32 max; rounding is monotonic and keeps 0, so the
-    // operand is the same fp16 value).
+    // operand is the same fp16 value).  Hidden tiles that are not computed
+    // enter as zeros.
     __device__ __forceinline__ v4f layer2(const v4f acc[4]) const {
         v4f u = {0.f, 0.f, 0.f, 0.f};
         const v8h zero = {};
@@ -302,13 +322,14 @@ struct MlpF16 {
         for (int p = 0; p < 2; ++p) {
             v8f x;
 #pragma unroll
-            for (int s = 0; s < 8; ++s) x[s] = acc[2 * p + s / 4][s % 4];
+            for (int s = 0; s < 8; ++s) x[s] = 2 * p + s / 4 < NT ? acc[2 * p + s / 4][s % 4] : 0.f;
             const v8h h = __builtin_elementwise_max(__builtin_convertvector(x, v8h), zero);
             u = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2[p], h, u, 0, 0, 0);
         }
         return u;
     }
 };
+using MlpF16 = MlpF16M<kC, kH>;
 
 // Scaled fp16 activations with split fp16 weights (for fp32 states).  The
 // features and the hidden units are rounded to fp16 after a scaling by 2^-8
@@ -319,14 +340,6 @@ struct MlpF16 {
 // activation split.  The activations keep fp16's 2^-12 relative rounding,
 // the weights about 2^-22.
 constexpr float kF16ActScale = 1.f / 256.f;
-
-// Feature order of a model with C channels (C <= 16, a multiple of 4): slot
-// s < 4 of lane group g is state channel 4g + s, slot s >= 4 perception
-// channel 4g + s - 4; lane groups g >= C / 4 hold no channel.
-template <int C>
-__device__ __forceinline__ int feature_of_c(int slot, int g) {
-    return slot < 4 ? 4 * g + slot : C + 4 * g + (slot - 4);
-}
 
 // C / H: the model's size.  The lane layout is that of C = 16, H = 64; a
 // smaller model (C = 12, H = 48 of the paper's ablation, supplement S10)
@@ -469,10 +482,6 @@ __device__ __forceinline__ uint64_t select_ballot(const FireBallots &f, uint32_t
     return (b & 4u) ? w47 : w03;
 }
 
-template <typename T> struct CellChunks;
-template <> struct CellChunks<float> { static constexpr int N = 4; };    // 16 B = 4 channels
-template <> struct CellChunks<__half> { static constexpr int N = 2; };   // 16 B = 8 channels
-
 // Plane stride rounded up to 16 words (256 B): measured on gfx950, strides of
 // 2, 4 and 12 words mod 16 left the 16-lane plane reads with ~20x more LDS
 // bank-conflict cycles than this choice.
@@ -493,6 +502,45 @@ constexpr int kRsrcWord3 = 0x00020000;      // raw buffer, 32-bit data format
 __device__ __forceinline__ Rsrc make_rsrc(const void *base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, kRsrcWord3);
 }
+
+// The chunks in which a cell of C channels moves between memory and LDS: 16
+// bytes (4 fp32 or 8 fp16 channels), or 8 bytes where a cell is no multiple of
+// 16 (fp16, C = 12).  N chunks cover 16 channels, of which the cell fills
+// kUsed; the loads of the others take the out-of-range offset and read as zero.
+template <typename T, int C> struct CellChunk {
+    static constexpr int kBytes = C * (int)sizeof(T) % 16 == 0 ? 16 : 8;
+    static constexpr int N = kC * (int)sizeof(T) / kBytes;
+    static constexpr int kUsed = C * (int)sizeof(T) / kBytes;
+    static_assert(C * (int)sizeof(T) % kBytes == 0 && kUsed <= N, "whole chunks");
+    __device__ static __forceinline__ uint4 load(Rsrc r, uint32_t off) {
+        if constexpr (kBytes == 16) {
+            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+            return make_uint4(x[0], x[1], x[2], x[3]);
+        } else {
+            const v2u x = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+            return make_uint4(x[0], x[1], 0u, 0u);
+        }
+    }
+    // Chunk q of a cell into LDS channel-quad planes of fp32 (16-byte words,
+    // `stride` apart).
+    __device__ static __forceinline__ void put(float4 *planes, int stride, int q, int slot,
+                                               const uint4 &c) {
+        if constexpr (sizeof(T) == 4) {
+            planes[q * stride + slot] = make_float4(__uint_as_float(c.x), __uint_as_float(c.y),
+                                                    __uint_as_float(c.z), __uint_as_float(c.w));
+        } else if constexpr (kBytes == 8) {
+            float f[4];
+            Storage<__half>::unpack_pair(c.x, f[0], f[1]);
+            Storage<__half>::unpack_pair(c.y, f[2], f[3]);
+            planes[q * stride + slot] = make_float4(f[0], f[1], f[2], f[3]);
+        } else {
+            float f[8];
+            Storage<__half>::unpack(c, f);
+            planes[(2 * q) * stride + slot] = make_float4(f[0], f[1], f[2], f[3]);
+            planes[(2 * q + 1) * stride + slot] = make_float4(f[4], f[5], f[6], f[7]);
+        }
+    }
+};
 
 // Residual update and store of the lane's 4 channels (fp32 values, stored in
 // the storage type) through the tile's store descriptor; `off` is the byte

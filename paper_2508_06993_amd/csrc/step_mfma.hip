@@ -100,10 +100,10 @@ __device__ __forceinline__ int64_t xcd_item(int64_t u, int grid) {
 // offset and read as zero.
 template <typename T, int HY, int C = kC>
 struct RowLoader {
-    static constexpr int NQ = CellChunks<T>::N;
+    using Ch = CellChunk<T, C>;
+    static constexpr int NQ = Ch::N;
     static constexpr int kCellBytes = C * (int)sizeof(T);
-    static constexpr int kChunks = kCellBytes / 16;
-    static_assert(kCellBytes % 16 == 0 && kChunks <= NQ, "whole 16-byte chunks");
+    static constexpr int kChunks = Ch::kUsed;
     static constexpr int kCellsPerBody = 64 / NQ;            // cells per body load
     static constexpr int kBodyPerRow = kTileW / kCellsPerBody;
     static constexpr int kRowsPerSide = 64 / (2 * NQ);       // rows per side load
@@ -140,7 +140,7 @@ struct RowLoader {
         const int base_row = gy0 > 0 ? gy0 : 0;
         const uint32_t row_bytes = (uint32_t)dw * kCellBytes;
         const int cell = body_cell(lane);
-        const uint32_t lane_off = (uint32_t)(cell * kCellBytes + body_chunk(lane) * 16);
+        const uint32_t lane_off = (uint32_t)(cell * kCellBytes + body_chunk(lane) * Ch::kBytes);
         Offsets r;
 #pragma unroll
         for (int k = 0; k < kBodySlots; ++k) {
@@ -159,7 +159,7 @@ struct RowLoader {
         const bool ok =
             s < kSide && row < HY && gy >= 0 && gx >= 0 && gx < dw && lane % NQ < kChunks;
         const uint32_t off = (uint32_t)(gy - base_row) * row_bytes + (uint32_t)gx * kCellBytes +
-                             (uint32_t)(lane % NQ) * 16;
+                             (uint32_t)(lane % NQ) * Ch::kBytes;
         r.o[kBodySlots] = ok ? off : kOut;
         return r;
     }
@@ -181,8 +181,7 @@ struct RowLoader {
                                  (uint32_t)rows * row_bytes);
 #pragma unroll
         for (int k = 0; k <= kBodySlots; ++k) {
-            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, of.o[k], 0, 0);
-            v[k] = make_uint4(x[0], x[1], x[2], x[3]);
+            v[k] = Ch::load(r, of.o[k]);
         }
     }
     __device__ __forceinline__ void issue(const T *__restrict__ src, int z, int dd, int dh, int dw,
@@ -190,16 +189,8 @@ struct RowLoader {
         issue_at(src, offsets(dw, y0, x0), z, dd, dh, dw, y0, active);
     }
 
-__device__ __forceinline__ static void put(float4 *planes, int q, int cell, const uint4 &c) {
-        if constexpr (NQ == 4) {
-            planes[q * PS + cell] = make_float4(__uint_as_float(c.x), __uint_as_float(c.y),
-                                                __uint_as_float(c.z), __uint_as_float(c.w));
-        } else {
-            float f[8];
-            Storage<__half>::unpack(c, f);
-            planes[(2 * q) * PS + cell] = make_float4(f[0], f[1], f[2], f[3]);
-            planes[(2 * q + 1) * PS + cell] = make_float4(f[4], f[5], f[6], f[7]);
-        }
+    __device__ __forceinline__ static void put(float4 *planes, int q, int cell, const uint4 &c) {
+        Ch::put(planes, PS, q, cell, c);
     }
 
     // LDS slot that is never read (plane padding): target of the writes of
@@ -269,7 +260,7 @@ __device__ __forceinline__ static void put(float4 *planes, int q, int cell, cons
         const int cbase = base_row / fy;
         const uint32_t crow_bytes = (uint32_t)cdw * kCellBytes;
         const int cell = body_cell(lane);
-        const uint32_t chunk_off = (uint32_t)body_chunk(lane) * 16;
+        const uint32_t chunk_off = (uint32_t)body_chunk(lane) * Ch::kBytes;
         UpOffsets<NIN> r;
 #pragma unroll
         for (int k = 0; k < kBodySlots; ++k) {
@@ -288,7 +279,7 @@ __device__ __forceinline__ static void put(float4 *planes, int q, int cell, cons
             const int gx = ((lane / NQ) & 1) ? x0 + kTileW : x0 - 1;
             const bool ok = s < kSide && row < HY && gy >= 0 && gx >= 0 && gx < dw;
             const uint32_t off = (uint32_t)(gy / fy - cbase) * crow_bytes +
-                                 (uint32_t)(gx / fx) * kCellBytes + (uint32_t)(lane % NQ) * 16;
+                                 (uint32_t)(gx / fx) * kCellBytes + (uint32_t)(lane % NQ) * Ch::kBytes;
             r.o[kBodySlots] = ok ? off : kOut;
         }
         const uint32_t irow_bytes = (uint32_t)dw * NIN * (uint32_t)sizeof(T);
@@ -333,8 +324,7 @@ __device__ __forceinline__ static void put(float4 *planes, int q, int cell, cons
                                  (uint32_t)crows * crow_bytes);
 #pragma unroll
         for (int k = 0; k <= kBodySlots; ++k) {
-            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, of.o[k], 0, 0);
-            v[k] = make_uint4(x[0], x[1], x[2], x[3]);
+            v[k] = Ch::load(r, of.o[k]);
         }
         const uint32_t irow_bytes = (uint32_t)dw * NIN * (uint32_t)sizeof(T);
         const Rsrc ri = make_rsrc(img + ((int64_t)max(z, 0) * dh + base_row) * dw * NIN,
@@ -583,10 +573,10 @@ __device__ __forceinline__ void load_conv_2d(const float *__restrict__ conv_w,
 // channels with zeros.
 template <typename T, int C = kC>
 struct RowStream {
-    static constexpr int NQ = CellChunks<T>::N;
+    using Ch = CellChunk<T, C>;
+    static constexpr int NQ = Ch::N;
     static constexpr int kCellBytes = C * (int)sizeof(T);
-    static constexpr int kChunks = kCellBytes / 16;
-    static_assert(kCellBytes % 16 == 0 && kChunks <= NQ, "whole 16-byte chunks");
+    static constexpr int kChunks = Ch::kUsed;
     static constexpr int kCellsPerBody = 64 / NQ;
     static constexpr int kBody = kTileW / kCellsPerBody;
     static constexpr int kDummy = kHaloW;                 // never-read slot
@@ -604,30 +594,20 @@ struct RowStream {
         for (int k = 0; k < kBody; ++k) {
             const int cx = x0 + k * kCellsPerBody + cell;
             const uint32_t off = chunk < kChunks && cx >= 0 && cx < dw
-                                     ? (uint32_t)cx * kCellBytes + (uint32_t)chunk * 16
+                                     ? (uint32_t)cx * kCellBytes + (uint32_t)chunk * Ch::kBytes
                                      : kOut;
-            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-            v[k] = make_uint4(x[0], x[1], x[2], x[3]);
+            v[k] = Ch::load(r, off);
         }
         const int cx = lane < NQ ? x0 - 1 : x0 + kTileW;
         const bool ok = lane < 2 * NQ && lane % NQ < kChunks && cx >= 0 && cx < dw;
-        const uint32_t off = ok ? (uint32_t)cx * kCellBytes + (uint32_t)(lane % NQ) * 16 : kOut;
-        const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-        v[kBody] = make_uint4(x[0], x[1], x[2], x[3]);
+        const uint32_t off = ok ? (uint32_t)cx * kCellBytes + (uint32_t)(lane % NQ) * Ch::kBytes : kOut;
+        v[kBody] = Ch::load(r, off);
     }
 
     // LDS: four channel-quad planes of PS 16-byte words, fp32; slot 0 is the
     // left halo cell, 1..32 the strip, 33 the right halo cell.
     __device__ static __forceinline__ void put(float4 *planes, int q, int slot, const uint4 &c) {
-        if constexpr (NQ == 4) {
-            planes[q * PS + slot] = make_float4(__uint_as_float(c.x), __uint_as_float(c.y),
-                                                __uint_as_float(c.z), __uint_as_float(c.w));
-        } else {
-            float f[8];
-            Storage<__half>::unpack(c, f);
-            planes[(2 * q) * PS + slot] = make_float4(f[0], f[1], f[2], f[3]);
-            planes[(2 * q + 1) * PS + slot] = make_float4(f[4], f[5], f[6], f[7]);
-        }
+        Ch::put(planes, PS, q, slot, c);
     }
 
     __device__ __forceinline__ void commit(float4 *planes) const {
@@ -665,18 +645,16 @@ struct RowStream {
         for (int k = 0; k < kBody; ++k) {
             const int cx = x0 + k * kCellsPerBody + cell;
             const uint32_t off = chunk < kChunks && cx >= 0 && cx < dw
-                                     ? (uint32_t)(cx / fx) * kCellBytes + (uint32_t)chunk * 16
+                                     ? (uint32_t)(cx / fx) * kCellBytes + (uint32_t)chunk * Ch::kBytes
                                      : kOut;
-            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-            v[k] = make_uint4(x[0], x[1], x[2], x[3]);
+            v[k] = Ch::load(r, off);
         }
         {
             const int cx = lane < NQ ? x0 - 1 : x0 + kTileW;
             const bool ok = lane < 2 * NQ && lane % NQ < kChunks && cx >= 0 && cx < dw;
             const uint32_t off =
-                ok ? (uint32_t)(cx / fx) * kCellBytes + (uint32_t)(lane % NQ) * 16 : kOut;
-            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-            v[kBody] = make_uint4(x[0], x[1], x[2], x[3]);
+                ok ? (uint32_t)(cx / fx) * kCellBytes + (uint32_t)(lane % NQ) * Ch::kBytes : kOut;
+            v[kBody] = Ch::load(r, off);
         }
         const Rsrc ri = make_rsrc(img + (int64_t)(row_ok ? y : 0) * dw * NIN,
                                   row_ok ? (uint32_t)dw * NIN * (uint32_t)sizeof(T) : 0u);
@@ -1026,11 +1004,11 @@ __global__ __launch_bounds__(64, k2WavesPerSimd) void nca_step2_mfma_2d_rows(
         for (int kk = 0; kk < RS::kBody; ++kk) {
             const int cx = x + kk * RS::kCellsPerBody + cell;
             uc.body[kk] = chunk < RS::kChunks && cx >= 0 && cx < dw
-                              ? (uint32_t)(cx / up_fx) * kCellBytes + (uint32_t)chunk * 16 : kOut;
+                              ? (uint32_t)(cx / up_fx) * kCellBytes + (uint32_t)chunk * RS::Ch::kBytes : kOut;
         }
         const int cx = lane < RS::NQ ? x - 1 : x + kTileW;
         uc.side = lane < 2 * RS::NQ && lane % RS::NQ < RS::kChunks && cx >= 0 && cx < dw
-                      ? (uint32_t)(cx / up_fx) * kCellBytes + (uint32_t)(lane % RS::NQ) * 16 : kOut;
+                      ? (uint32_t)(cx / up_fx) * kCellBytes + (uint32_t)(lane % RS::NQ) * RS::Ch::kBytes : kOut;
 #pragma unroll
         for (int j = 0; j < Img::kImg; ++j) {
             const int e = lane + 64 * j;
@@ -1894,9 +1872,13 @@ RowsPlan pair_plan(const StepArgs &a) {
 }
 
 // The ablation's C = 12, H = 48 model (supplement S10) on the kernels of
-// C = 16: fp32 states (the 2D row kernels and the 3D step), scaled fp16 MLP,
-// the lanes of channel quad 3 and hidden tile 3 idle.
+// C = 16: the 2D row kernels and the 3D step with an fp32 ring, the default
+// operands, the lanes of channel quad 3 and hidden tile 3 idle.  (fp16 3D: the
+// fp16-ring step would sum the perception in fp16, which these steps never
+// did.  On a 48 x 120 x 216 clip the fp32 ring took the finest level's step
+// from 105 us on the generic kernel to the figure beside launch_3d.)
 using MlpC12 = MlpF16SM<12, 48>;
+using MlpC12h = MlpF16M<12, 48>;
 bool is_c12(const StepArgs &a) { return a.channels == 12 && a.hidden == 48; }
 bool is_c16(const StepArgs &a) { return a.channels == kC && a.hidden == kH; }
 
@@ -2036,8 +2018,7 @@ hipError_t dispatch(const StepArgs &a, Layout2d layout, const void *src, void *d
     if (a.ndim == 2) {
         if (a.n_in == 1) return launch_2d<T, 1, Mlp>(a, layout, src, dst, stream);
         if (a.n_in == 3) return launch_2d<T, 3, Mlp>(a, layout, src, dst, stream);
-    } else if constexpr (Mlp::kChannels == kC || std::is_same_v<T, float>) {
-        // 3D: C = 16, H = 64, or fp32 states of C = 12, H = 48
+    } else {
         if (a.n_in == 1) return launch_3d<T, 1, Mlp>(a, src, dst, stream);
         if (a.n_in == 3) return launch_3d<T, 3, Mlp>(a, src, dst, stream);
     }
@@ -2092,8 +2073,7 @@ hipError_t launch_step2_mfma_up(const StepArgs &a, MfmaMlp mlp, Layout2d layout,
 
 bool step_mfma_serves(const StepArgs &a, Layout2d layout) {
     if (is_c16(a)) return true;
-    return is_c12(a) && a.dtype == Dtype::F32 && (a.ndim == 3 || uses_rows(a, layout)) &&
-           mfma_fits(a);
+    return is_c12(a) && (a.ndim == 3 || uses_rows(a, layout)) && mfma_fits(a);
 }
 
 bool step_mfma_fuses_upsample(const StepArgs &a, MfmaMlp mlp, Layout2d layout) {
@@ -2115,6 +2095,15 @@ hipError_t launch_step_mfma_up(const StepArgs &a, Layout2d layout, const void *c
         if (a.n_in == 3)
             return launch_3d_f16_up<3>(a, coarse, coarse_h, coarse_w, fz, fy, fx, img, dst,
                                        stream);
+        return hipErrorInvalidValue;
+    }
+    if (is_c12(a) && a.dtype == Dtype::F16) {
+        if (a.n_in == 1)
+            return launch_rows<__half, 1, MlpC12h, true>(a, coarse, dst, img, coarse_w, fy, fx,
+                                                         stream);
+        if (a.n_in == 3)
+            return launch_rows<__half, 3, MlpC12h, true>(a, coarse, dst, img, coarse_w, fy, fx,
+                                                         stream);
         return hipErrorInvalidValue;
     }
     if (is_c12(a)) {
@@ -2149,7 +2138,8 @@ hipError_t launch_step_mfma(const StepArgs &a, MfmaMlp mlp, Layout2d layout, con
     if (!mfma_fits(a)) return launch_step_valu(a, src, dst, stream);
     if (is_c12(a)) {
         if (!step_mfma_serves(a, layout) || mlp != MfmaMlp::Default) return hipErrorInvalidValue;
-        return dispatch<float, MlpC12>(a, layout, src, dst, stream);
+        return a.dtype == Dtype::F32 ? dispatch<float, MlpC12>(a, layout, src, dst, stream)
+                                     : dispatch<__half, MlpC12h>(a, layout, src, dst, stream);
     }
     if (!is_c16(a)) return hipErrorInvalidValue;
     if (mlp == MfmaMlp::Default)

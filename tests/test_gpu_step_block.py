@@ -16,7 +16,7 @@ from synthetic import TINY_2D, make_image, make_weights, scaled
 
 pytestmark = pytest.mark.gpu
 
-KINDS = [("f32", 16, 64), ("f32", 12, 48), ("f16", 16, 64)]
+KINDS = [("f32", 16, 64), ("f32", 12, 48), ("f16", 16, 64), ("f16", 12, 48)]
 
 
 def _models(dtype, c, h, n_in):
