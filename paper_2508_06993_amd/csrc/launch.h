@@ -5,6 +5,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <atomic>
+
 #include "device_common.h"
 
 namespace octnca {
@@ -196,5 +199,50 @@ hipError_t launch_step2_mfma_up(const StepArgs &a, MfmaMlp mlp, Layout2d layout,
 hipError_t launch_step_mfma_up(const StepArgs &a, Layout2d layout, const void *coarse,
                                int coarse_h, int coarse_w, int fz, int fy, int fx,
                                const void *img, void *dst, hipStream_t stream);
+
+// Compute units of the current device, cached per device.  Host threads may
+// call this concurrently: racing first calls store the same value.
+inline int device_cus() {
+    static std::atomic<int> cached[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int n = cached[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            n <= 0)
+            n = 256;
+        cached[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+// Output planes per 3D work item, chosen per launch: the run length r in
+// 1 .. max_run that minimises ceil(items(r) / slots) * (min(r, depth) + extra,
+// rounded up to whole groups), the work of the most loaded block slot
+// (grid-stride rounds times the planes a work item streams, `extra` halo and
+// set-up planes included); ties go to the longer run.  Short runs spread small
+// levels over the chip at the cost of reading their halo planes again; long
+// runs stream large levels with little re-reading.  group: a plane loop that
+// is unrolled streams whole groups of planes.
+inline int pick_zrun(int64_t tiles, int64_t depth, int64_t slots, int extra, int group,
+                     int max_run) {
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int r = 1; r <= max_run; ++r) {
+        const int64_t items = tiles * ((depth + r - 1) / r);
+        const int64_t planes = (std::min<int64_t>(r, depth) + extra + group - 1) / group * group;
+        const int64_t cost = (items + slots - 1) / slots * planes;
+        if (cost <= best_cost) {
+            best_cost = cost;
+            best = r;
+        }
+    }
+    return best;
+}
+// The fp16 3D step of C = 16, H = 64 models with fp16 MLP operands
+// (step_3d_f16.hip); img null: src is a state of the level, else the first step
+// fused with the upsample from the coarse state src (planes of cdh x cdw cells).
+hipError_t launch_step_3d_f16(const StepArgs &a, const void *src, void *dst, const void *img,
+                              int cdh, int cdw, int fz, int fy, int fx, hipStream_t stream);
 
 }  // namespace octnca

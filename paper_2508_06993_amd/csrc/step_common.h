@@ -486,6 +486,22 @@ __device__ __forceinline__ uint64_t select_ballot(const FireBallots &f, uint32_t
 // 2, 4 and 12 words mod 16 left the 16-lane plane reads with ~20x more LDS
 // bank-conflict cycles than this choice.
 constexpr int plane_stride(int cells) { return (cells + 15) / 16 * 16; }
+// Workgroups go to the eight XCDs in turn (blockIdx % 8) and each XCD has an
+// L2 of its own.  The grid-stride loops of the 3D step kernels map their index
+// u to a work item such that the workgroups of one XCD that run at the same
+// time take consecutive items (neighbouring tiles of one z run), which then
+// find each other's halo rows and columns in that L2 instead of fetching the
+// same lines again (measured: 1% off the video step; the 2D row kernel, where
+// it measured 2% slower, keeps the plain order).  A bijection of
+// [0, rounds * grid) when grid % 8 == 0, the identity otherwise.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int64_t xcd_item(int64_t u, int grid) {
+    if (grid % kXcds) return u;
+    const int64_t r = u / grid;
+    const int b = (int)(u - r * grid);
+    return (r * kXcds + b % kXcds) * (grid / kXcds) + b / kXcds;
+}
+
 // Buffer resources: every global access of the step kernel goes through a
 // raw buffer descriptor whose range covers only the rows a tile may touch;
 // an out-of-range offset (0xffffffff is used for cells outside the grid)

@@ -79,22 +79,6 @@ struct FireBits {
 constexpr int kTileW = 32;
 constexpr int kHaloW = kTileW + 2;
 
-// Workgroups go to the eight XCDs in turn (blockIdx % 8) and each XCD has an
-// L2 of its own.  The grid-stride loops of the 3D step kernels map their index
-// u to a work item such that the workgroups of one XCD that run at the same
-// time take consecutive items (neighbouring tiles of one z run), which then
-// find each other's halo rows and columns in that L2 instead of fetching the
-// same lines again (measured: 1% off the video step; the 2D row kernel, where
-// it measured 2% slower, keeps the plain order).  A bijection of
-// [0, rounds * grid) when grid % 8 == 0, the identity otherwise.
-constexpr int kXcds = 8;
-__device__ __forceinline__ int64_t xcd_item(int64_t u, int grid) {
-    if (grid % kXcds) return u;
-    const int64_t r = u / grid;
-    const int b = (int)(u - r * grid);
-    return (r * kXcds + b % kXcds) * (grid / kXcds) + b / kXcds;
-}
-
 // C: channels of a cell; a cell fills kChunks of the NQ 16-byte chunks, the
 // loads of the others (channel quad 3 when C = 12) take the out-of-range
 // offset and read as zero.
@@ -213,160 +197,6 @@ struct RowLoader {
         const int row = s * kRowsPerSide + lane / (2 * NQ);
         const int slot = row * kHaloW + (((lane / NQ) & 1) ? kHaloW - 1 : 0);
         put(planes, lane % NQ, (s < kSide && row < HY) ? slot : kDummyCell, v[kBodySlots]);
-    }
-
-    // fp16 rows kept as fp16 in LDS: four channel-quad planes of 8-byte words
-    // (channels 4q..4q+3 of a cell); a 16-byte chunk c (channels 8c..8c+7)
-    // is split between quad planes 2c and 2c+1.  Same slots as commit().
-    // Quad plane stride of the fp16 planes (8-byte words): 16 mod 32, so the
-    // planes of lane groups g and g + 1 start 128 bytes apart modulo 256 (the
-    // 8-byte reads of one wave then hit disjoint banks; measured 8.8x fewer
-    // bank-conflict cycles than a multiple of 32).
-    static constexpr int PS16 = (HY * kHaloW + 1 + 15) / 32 * 32 + 16;
-    static_assert(PS16 > kDummyCell, "fp16 plane padding holds the dummy slot");
-    __device__ static __forceinline__ void put_raw(uint2 *planes, int c, int cell, const uint4 &x) {
-        planes[(2 * c) * PS16 + cell] = make_uint2(x.x, x.y);
-        planes[(2 * c + 1) * PS16 + cell] = make_uint2(x.z, x.w);
-    }
-
-    // Image elements of a tile's rows for the fused upsample (one per thread
-    // and load).
-    static constexpr int kThreadsPerBlock = 256;
-    template <int NIN>
-    struct Image {
-        static constexpr int kElems = HY * kHaloW * NIN;
-        static constexpr int kImg = (kElems + kThreadsPerBlock - 1) / kThreadsPerBlock;
-        uint32_t e[kImg];
-    };
-
-    // Per-lane byte offsets of the fused-upsample loads within the coarse rows
-    // and the image rows a tile may touch (kOut for unused slots and cells
-    // outside the grid): like offsets(), they depend on the tile only and are
-    // computed once per work item (the per-lane divisions by fx and fy no
-    // longer run per plane).
-    template <int NIN>
-    struct UpOffsets {
-        uint32_t o[kBodySlots + 1];
-        uint32_t img[Image<NIN>::kImg];
-    };
-    template <int NIN>
-    __device__ __forceinline__ static UpOffsets<NIN> up_offsets(int cdw, int fy, int fx, int dw,
-                                                                int y0, int x0) {
-        static_assert(C == kC, "the fused upsample serves C = 16");
-        const int lane = threadIdx.x & 63;
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int gy0 = y0 - 1;
-        const int base_row = gy0 > 0 ? gy0 : 0;
-        const int cbase = base_row / fy;
-        const uint32_t crow_bytes = (uint32_t)cdw * kCellBytes;
-        const int cell = body_cell(lane);
-        const uint32_t chunk_off = (uint32_t)body_chunk(lane) * Ch::kBytes;
-        UpOffsets<NIN> r;
-#pragma unroll
-        for (int k = 0; k < kBodySlots; ++k) {
-            const int J = wave + 4 * k;
-            const int gy = gy0 + J / kBodyPerRow;
-            const int cx = x0 + (J % kBodyPerRow) * kCellsPerBody + cell;
-            const bool ok = J < kBody && gy >= 0 && cx < dw;
-            const uint32_t off = (uint32_t)(gy / fy - cbase) * crow_bytes +
-                                 (uint32_t)(cx / fx) * kCellBytes + chunk_off;
-            r.o[k] = ok ? off : kOut;
-        }
-        {
-            const int s = 3 - wave;
-            const int row = s * kRowsPerSide + lane / (2 * NQ);
-            const int gy = gy0 + row;
-            const int gx = ((lane / NQ) & 1) ? x0 + kTileW : x0 - 1;
-            const bool ok = s < kSide && row < HY && gy >= 0 && gx >= 0 && gx < dw;
-            const uint32_t off = (uint32_t)(gy / fy - cbase) * crow_bytes +
-                                 (uint32_t)(gx / fx) * kCellBytes + (uint32_t)(lane % NQ) * Ch::kBytes;
-            r.o[kBodySlots] = ok ? off : kOut;
-        }
-        const uint32_t irow_bytes = (uint32_t)dw * NIN * (uint32_t)sizeof(T);
-#pragma unroll
-        for (int j = 0; j < Image<NIN>::kImg; ++j) {
-            const int e = (int)threadIdx.x + kThreadsPerBlock * j;
-            const int row = e / (kHaloW * NIN);
-            const int rem = e - row * (kHaloW * NIN);
-            const int gy = gy0 + row;
-            const int gx = x0 - 1 + rem / NIN;
-            const bool ok = e < Image<NIN>::kElems && gy >= 0 && gx >= 0 && gx < dw;
-            const uint32_t off = (uint32_t)(gy - base_row) * irow_bytes +
-                                 (uint32_t)(gx * NIN + rem % NIN) * (uint32_t)sizeof(T);
-            r.img[j] = ok ? off : kOut;
-        }
-        return r;
-    }
-
-    // Upsample + inject fused into the load (3D first step of a level; fp16
-    // planes): plane z, row gy and cell gx of the fine level come from the
-    // coarse state's plane z / fz, row gy / fy and cell gx / fx; the NIN input
-    // channels from the fine image, one element per thread and load, written
-    // over channel quad 0 by commit_up_raw.  `of` holds the lane offsets of the
-    // tile whose interior starts at (y0, x0) (from up_offsets()); rows outside
-    // the grid and z outside [0, dd) read as zero through the descriptors'
-    // ranges (the fine height is a multiple of fy, so a row below the grid
-    // maps past the coarse rows covered).
-    template <int NIN>
-    __device__ __forceinline__ void issue_up(const T *__restrict__ coarse, int cdh, int cdw,
-                                             int fz, int fy, const T *__restrict__ img,
-                                             const UpOffsets<NIN> &of, Image<NIN> &im, int z,
-                                             int dd, int dh, int dw, int y0, bool active = true) {
-        const int gy0 = y0 - 1;
-        const int base_row = gy0 > 0 ? gy0 : 0;
-        const int rows =
-            (active && z >= 0 && z < dd) ? max(0, min(gy0 + HY, dh) - base_row) : 0;
-        // coarse rows base_row / fy .. (base_row + rows - 1) / fy of plane z / fz
-        const int cbase = base_row / fy;
-        const int crows = rows > 0 ? (base_row + rows - 1) / fy - cbase + 1 : 0;
-        const uint32_t crow_bytes = (uint32_t)cdw * kCellBytes;
-        const Rsrc r = make_rsrc(coarse + ((int64_t)(max(z, 0) / fz) * cdh + cbase) * cdw * C,
-                                 (uint32_t)crows * crow_bytes);
-#pragma unroll
-        for (int k = 0; k <= kBodySlots; ++k) {
-            v[k] = Ch::load(r, of.o[k]);
-        }
-        const uint32_t irow_bytes = (uint32_t)dw * NIN * (uint32_t)sizeof(T);
-        const Rsrc ri = make_rsrc(img + ((int64_t)max(z, 0) * dh + base_row) * dw * NIN,
-                                  (uint32_t)rows * irow_bytes);
-#pragma unroll
-        for (int j = 0; j < Image<NIN>::kImg; ++j)
-            im.e[j] = __builtin_amdgcn_raw_buffer_load_b16(ri, of.img[j], 0, 0);
-    }
-
-    // Called by every thread of the block: the coarse words of a cell and its
-    // image channels are written by different waves, so a barrier orders them.
-    template <int NIN>
-    __device__ __forceinline__ void commit_up_raw(uint2 *planes, const Image<NIN> &im) const {
-        commit_raw(planes);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < Image<NIN>::kImg; ++j) {
-            const int e = (int)threadIdx.x + kThreadsPerBlock * j;
-            const int row = e / (kHaloW * NIN);
-            const int rem = e - row * (kHaloW * NIN);
-            const int slot = e < Image<NIN>::kElems ? row * kHaloW + rem / NIN : kDummyCell;
-            reinterpret_cast<unsigned short *>(planes + slot)[rem % NIN] =
-                (unsigned short)im.e[j];   // channel quad plane 0
-        }
-    }
-
-    __device__ __forceinline__ void commit_raw(uint2 *planes) const {
-        static_assert(NQ == 2, "raw fp16 planes");
-        const int lane = threadIdx.x & 63;
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int cell = body_cell(lane), chunk = body_chunk(lane);
-#pragma unroll
-        for (int k = 0; k < kBodySlots; ++k) {
-            const int J = wave + 4 * k;
-            const int slot =
-                (J / kBodyPerRow) * kHaloW + 1 + (J % kBodyPerRow) * kCellsPerBody + cell;
-            put_raw(planes, chunk, J < kBody ? slot : kDummyCell, v[k]);
-        }
-        const int s = 3 - wave;
-        const int row = s * kRowsPerSide + lane / (2 * NQ);
-        const int slot = row * kHaloW + (((lane / NQ) & 1) ? kHaloW - 1 : 0);
-        put_raw(planes, lane % NQ, (s < kSide && row < HY) ? slot : kDummyCell, v[kBodySlots]);
     }
 };
 
@@ -1257,7 +1087,6 @@ constexpr int k3TY = 8;
 // takes runs of up to 256 planes (16 KB of fire words per block: 52 KB, still
 // 3 blocks per CU).
 constexpr int k3ZRun = 128;
-constexpr int k3hZRun = 256;
 // Work item i of a 3D step is tile (tx, ty) of z run zr, with
 // i = (zr * tiles_y + ty) * tiles_x + tx.
 
@@ -1497,311 +1326,7 @@ __global__ __launch_bounds__(kThreads, 2) void nca_step_mfma_3d(
     }
 }
 
-// ---------------------------------------------------------------------------
-// 3D step for fp16 states with the fp16 MLP: the same z streaming as
-// nca_step_mfma_3d, but the ring holds the planes as fp16 (8-byte channel
-// quads, half the LDS) and the perception sums are packed fp16 FMAs
-// (v_pk_fma_f16: two channels per instruction, half the VALU work of fp32
-// sums).  The features go to the fp16 MFMAs without conversion.  The sums
-// are rounded to fp16 after every tap; with fp16 storage this changes the
-// result by far less than the fp16 rounding of the stored state itself.
-// ---------------------------------------------------------------------------
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
-// (mask & a) | (~mask & b) in one instruction (the compiler builds it from
-// two ands, an and-or and the mask's complement)
-__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) {
-    uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(mask), "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ uint32_t as_u32(h2 v) { return __builtin_bit_cast(uint32_t, v); }
-
-constexpr int k3hBlocksPerCu = 3;
-// the upsample-fused variant: its extra set-up registers spill a few words
-// outside the plane loop at 3 blocks per CU
-constexpr int k3hUpBlocksPerCu = 3;
-
-// UP: the first step of a level fused with the upsample + inject: src is the
-// next coarser level's state (extent up_cdh x up_cdw per plane), upsampled by
-// (up_fz, up_fy, up_fx), with the input channels from up_img.
-// (The UP variant runs one step per level and needs more registers for its
-// extra loads: it is built for 2 blocks per CU, the plain one for 3.)
-// SEG: the launch also writes the two-class readout of the state it stores
-// (channel C - 1 > channel C - 2 in the stored fp16 values, ties and NaNs 0)
-// to seg; the finest level's last launch uses it.
-template <int NIN, bool ALIGNED, bool UP, bool SEG = false>
-__global__ __launch_bounds__(kThreads, UP ? k3hUpBlocksPerCu : k3hBlocksPerCu) void nca_step_mfma_3d_f16(
-    const __half *__restrict__ src, __half *__restrict__ dst, int dd, int dh, int dw,
-    int tiles_x, int tiles_y, int items, int zrun, const float *__restrict__ conv_w,
-    const float *__restrict__ conv_b, const float *__restrict__ w1, const float *__restrict__ b1,
-    const float *__restrict__ w2, uint32_t level, uint32_t step, uint32_t batch, uint64_t seed,
-    uint64_t threshold, const __half *__restrict__ up_img, int up_cdh, int up_cdw, int up_fz,
-    int up_fy, int up_fx, uint8_t *__restrict__ seg) {
-    using Loader = RowLoader<__half, k3TY + 2>;
-    __shared__ uint2 ring[3][4 * Loader::PS16];
-    __shared__ uint2 tapw[27][4];           // [tap][quad] fp16 conv weights of channels 4q..4q+3
-    // [wave][evaluation of the work item][b]: ballot b (k3hZRun / 4 evaluations
-    // at most: one per 4 or 8 planes)
-    __shared__ uint64_t fire_words[4][k3hZRun / 4][8];
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 15;
-    const int g = lane >> 4;
-
-    {
-        const int i = min((int)threadIdx.x, 27 * 4 - 1);
-        const int t = i / 4, q = i % 4;
-        const h2 lo = {(_Float16)conv_w[(4 * q + 0) * 27 + t], (_Float16)conv_w[(4 * q + 1) * 27 + t]};
-        const h2 hi = {(_Float16)conv_w[(4 * q + 2) * 27 + t], (_Float16)conv_w[(4 * q + 3) * 27 + t]};
-        if (threadIdx.x < 27 * 4) tapw[t][q] = make_uint2(as_u32(lo), as_u32(hi));
-    }
-    MlpF16 mlp;
-    mlp.load(w1, b1, w2, n, g, NIN);
-    h2 cb[2];
-    cb[0] = h2{(_Float16)conv_b[4 * g + 0], (_Float16)conv_b[4 * g + 1]};
-    cb[1] = h2{(_Float16)conv_b[4 * g + 2], (_Float16)conv_b[4 * g + 3]};
-    float one = 1.f;
-    mlp.pin_all();
-    pin(cb[0]);
-    pin(cb[1]);
-    pin(one);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    // fire evaluations as in nca_step_mfma_3d; ALIGNED (w % 8 == 0) makes the
-    // ballot and bit offsets of a lane's cells lane constants
-    constexpr int opr = ALIGNED ? 4 : 8;
-    constexpr int lg_opr = ALIGNED ? 2 : 3;
-    constexpr int planes_per_eval = 64 / (2 * opr);
-    constexpr int kCellBytes = Loader::kCellBytes;
-    const uint32_t row_bytes = (uint32_t)dw * kCellBytes;
-    int y0_cur = 0;   // the current item's first tile row (for the loads)
-    typename Loader::Offsets lofs;  // and its lane offsets (plain loads)
-    typename Loader::template UpOffsets<NIN> uofs;   // (fused upsample loads)
-    Loader ld;
-    typename Loader::template Image<NIN> im;   // used by UP only
-    auto issue = [&](int z, bool active) {
-        if constexpr (UP)
-            ld.template issue_up<NIN>(src, up_cdh, up_cdw, up_fz, up_fy, up_img, uofs, im, z,
-                                      dd, dh, dw, y0_cur, active);
-        else
-            ld.issue_at(src, lofs, z, dd, dh, dw, y0_cur, active);
-    };
-    auto commit = [&](uint2 *slot) {
-        if constexpr (UP)
-            ld.template commit_up_raw<NIN>(slot, im);
-        else
-            ld.commit_raw(slot);
-    };
-    int centre[4];
-#pragma unroll
-    for (int grp = 0; grp < 4; ++grp)
-        centre[grp] = g * Loader::PS16 + (2 * wave + (grp >> 1) + 1) * kHaloW + (grp & 1) * 16 + n + 1;
-
-    const int64_t span = ((int64_t)items + gridDim.x - 1) / gridDim.x * gridDim.x;
-    for (int64_t u = blockIdx.x; u < span; u += gridDim.x) {
-        const int64_t it = xcd_item(u, (int)gridDim.x);
-        if (it >= items) continue;                       // uniform over the block
-        const int tiles = tiles_x * tiles_y;
-        const int zr = (int)it / tiles;
-        const int rest = (int)it - zr * tiles;
-        const int tx = rest % tiles_x;
-        const int ty = rest / tiles_x;
-        const int y0 = ty * k3TY, x0 = tx * kTileW;
-        y0_cur = y0;
-        if constexpr (UP)
-            uofs = Loader::template up_offsets<NIN>(up_cdw, up_fy, up_fx, dw, y0, x0);
-        else
-            lofs = Loader::offsets(dw, y0, x0);
-        const int z_begin = zr * zrun;
-        const int z_end = min(dd, z_begin + zrun);
-        // store offsets of the lane's 4 cells within an output plane's tile rows
-        uint32_t offs[4];
-#pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-            const int x = x0 + (grp & 1) * 16 + n;
-            offs[grp] = x < dw ? (uint32_t)(2 * wave + (grp >> 1)) * row_bytes +
-                                     (uint32_t)x * kCellBytes + 8u * g
-                               : kOut;
-        }
-
-        // Rolling perception sums (bias included), channels (4g, 4g+1) in
-        // [.][0] and (4g+2, 4g+3) in [.][1]: A[(r - z_begin + 1) % 3] holds the
-        // sum of output plane r.  The plane loop is unrolled three times, so
-        // the three sums rotate roles instead of being moved; a run is padded
-        // to whole groups of three planes (the padding planes load nothing and
-        // store nothing).
-        h2 A[3][4][2];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int grp = 0; grp < 4; ++grp)
-#pragma unroll
-                for (int k = 0; k < 2; ++k) A[i][grp][k] = cb[k];
-
-        __syncthreads();
-        issue(z_begin - 1, true);
-        // All fire evaluations of the work item, before the plane loop (inside
-        // it they cost the loop registers): evaluation e covers output planes
-        // z_begin + e * planes_per_eval onwards.
-        for (int e = 0; z_begin + e * planes_per_eval < z_end; ++e) {
-            const int zo = z_begin + e * planes_per_eval;
-            const int zz = min(zo + (lane >> (lg_opr + 1)), dd - 1);
-            const uint64_t row =
-                (uint64_t)zz * dh + (uint64_t)(y0 + 2 * wave + ((lane >> lg_opr) & 1));
-            const FireBallots fb = fire_ballots(((row * dw + x0) >> 3) + (lane & (opr - 1)), step,
-                                                level, batch, seed, threshold);
-            uint64_t word = fb.w[0];
-#pragma unroll
-            for (int b = 1; b < 8; ++b) word = (lane & 7) == b ? fb.w[b] : word;
-            fire_words[wave][e][lane & 7] = word;
-        }
-        commit(ring[0]);
-        issue(z_begin, true);
-        __syncthreads();
-
-        // Plane p (j = (p - z_begin + 1) % 3) is in ring slot j, plane p - 1 in
-        // slot (j + 2) % 3, and plane p + 1 goes to slot (j + 1) % 3.
-        auto body = [&](int p, auto jc) {
-            constexpr int j = decltype(jc)::value;
-            constexpr int jm = (j + 2) % 3, jp = (j + 1) % 3;
-            h2 (&first)[4][2] = A[jp];    // output p + 1 (dz = -1 weights)
-            h2 (&second)[4][2] = A[j];    // output p (dz = 0)
-            h2 (&last)[4][2] = A[jm];     // output p - 1 (dz = +1), complete after
-            const uint2 *pl = ring[j];
-            int gq = g;
-            pin(gq);
-            uint2 sv[2][4], wv[2][3];
-            auto read_tap = [&](int t, uint2 (&s4)[4], uint2 (&w3)[3]) {
-                const int off = (t / 3 - 1) * kHaloW + (t % 3 - 1);
-                w3[0] = tapw[t][gq];
-                w3[1] = tapw[9 + t][gq];
-                w3[2] = tapw[18 + t][gq];
-#pragma unroll
-                for (int grp = 0; grp < 4; ++grp) s4[grp] = pl[centre[grp] + off];
-            };
-            read_tap(0, sv[0], wv[0]);
-#pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                if (t + 1 < 9) read_tap(t + 1, sv[(t + 1) & 1], wv[(t + 1) & 1]);
-                const uint2 *w3 = wv[t & 1];
-                const h2 a_m[2] = {as_h2(w3[0].x), as_h2(w3[0].y)};
-                const h2 a_0[2] = {as_h2(w3[1].x), as_h2(w3[1].y)};
-                const h2 a_p[2] = {as_h2(w3[2].x), as_h2(w3[2].y)};
-#pragma unroll
-                for (int grp = 0; grp < 4; ++grp) {
-                    const h2 v[2] = {as_h2(sv[t & 1][grp].x), as_h2(sv[t & 1][grp].y)};
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        first[grp][k] = __builtin_elementwise_fma(a_m[k], v[k],
-                                                                  t == 0 ? cb[k] : first[grp][k]);
-                        second[grp][k] = __builtin_elementwise_fma(a_0[k], v[k], second[grp][k]);
-                        last[grp][k] = __builtin_elementwise_fma(a_p[k], v[k], last[grp][k]);
-                    }
-                }
-#pragma unroll
-                for (int grp = 0; grp < 4; ++grp)
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        pin(first[grp][k]);
-                        pin(second[grp][k]);
-                        pin(last[grp][k]);
-                    }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-
-            const int zo = p - 1;
-            const bool out_ok = zo >= z_begin && zo < z_end;
-            const int zrel = min(max(zo - z_begin, 0), k3hZRun - 1);   // in range for any plane
-            const int phase = zrel & (planes_per_eval - 1);
-            const uint64_t *fwe = fire_words[wave][zrel / planes_per_eval];
-            const int slot0 = 2 * phase;
-            const Rsrc wr = make_rsrc(dst + ((int64_t)max(zo, 0) * dh + y0) * dw * kC,
-                                      out_ok ? (uint32_t)min(k3TY, dh - y0) * row_bytes : 0u);
-            const uint2 *own = ring[jm];
-            // ALIGNED: the bits of the lane's 4 cells of this plane, at 2 grp
-            uint32_t fw_lane = 0;
-            if constexpr (ALIGNED) fw_lane = (uint32_t)(fwe[n & 7] >> (slot0 * opr + (n >> 3)));
-#pragma unroll
-            for (int grp = 0; grp < 4; ++grp) {
-                const uint2 sp = own[centre[grp]];
-                const h2 s01 = as_h2(sp.x), s23 = as_h2(sp.y);
-                const v8h fh = {s01[0], s01[1], s23[0], s23[1], last[grp][0][0], last[grp][0][1],
-                                last[grp][1][0], last[grp][1][1]};
-                v4f acc[4];
-                mlp.layer1_h(fh, acc);
-                const v4f u = mlp.layer2(acc);
-                const int r = grp >> 1;
-                // all ones when the cell fires, else zero
-                uint32_t keep_new;
-                if constexpr (ALIGNED) {
-                    // cell n of the group is cell n % 8 of block (grp & 1) * 2 + n / 8 of its
-                    // row: bit (r * opr + (grp & 1) * 2) of fw_lane, i.e. bit 2 grp
-                    keep_new = (uint32_t)__builtin_amdgcn_sbfe((int)fw_lane, 2 * grp, 1);
-                } else {
-                    const int y = y0 + 2 * wave + r, x = x0 + (grp & 1) * 16 + n;
-                    const uint64_t idx = ((uint64_t)max(zo, 0) * dh + y) * dw + x;
-                    const uint64_t row_b0 = (((uint64_t)max(zo, 0) * dh + y) * dw + x0) >> 3;
-                    const uint64_t fw = fwe[idx & 7];
-                    keep_new = (fw >> ((slot0 + r) * opr + (int)((idx >> 3) - row_b0))) & 1 ? ~0u : 0u;
-                }
-                const uint32_t off = offs[grp];
-                // state + update in fp32, rounded once to fp16 (u = +0 keeps an
-                // input channel exactly); a cell that does not fire keeps its
-                // stored bits
-                // (as fmas with a register 1.0: one mixed-precision fma per value)
-                const h2 n01 = {(_Float16)fmaf(one, u[0], (float)s01[0]),
-                                (_Float16)fmaf(one, u[1], (float)s01[1])};
-                const h2 n23 = {(_Float16)fmaf(one, u[2], (float)s23[0]),
-                                (_Float16)fmaf(one, u[3], (float)s23[1])};
-                const v2u out = {bfi(keep_new, as_u32(n01), sp.x), bfi(keep_new, as_u32(n23), sp.y)};
-                __builtin_amdgcn_raw_buffer_store_b64(out, wr, off, 0, 0);
-                if constexpr (SEG) {
-                    // lanes of quad 3: out[1] holds channels 14 (low) and 15 (high)
-                    const h2 c1415 = as_h2(out[1]);
-                    const int x = x0 + (grp & 1) * 16 + n;
-                    const Rsrc sr = make_rsrc(seg + ((int64_t)max(zo, 0) * dh + y0) * dw,
-                                              out_ok ? (uint32_t)min(k3TY, dh - y0) * dw : 0u);
-                    const uint32_t so =
-                        g == 3 && x < dw ? (uint32_t)(2 * wave + (grp >> 1)) * dw + x : kOut;
-                    __builtin_amdgcn_raw_buffer_store_b8(
-                        (unsigned char)((float)c1415[1] > (float)c1415[0] ? 1 : 0), sr, so, 0, 0);
-                }
-            }
-
-            commit(ring[jp]);
-            issue(p + 2, p + 2 <= z_end);
-            __syncthreads();
-        };
-        for (int p0 = z_begin - 1; p0 <= z_end; p0 += 3) {
-            body(p0, std::integral_constant<int, 0>{});
-            body(p0 + 1, std::integral_constant<int, 1>{});
-            body(p0 + 2, std::integral_constant<int, 2>{});
-        }
-    }
-}
-
 // ==== host side: launch plans and dispatch ====
-
-// Compute units of the current device, cached per device.  Host threads may
-// call this concurrently: racing first calls store the same value.
-int device_cus() {
-    static std::atomic<int> cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int n = cached[dev].load(std::memory_order_relaxed);
-    if (n == 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            n <= 0)
-            n = 256;
-        cached[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
 
 constexpr int kBlocksPerCu = 2;
 
@@ -1930,54 +1455,19 @@ hipError_t launch_2d(const StepArgs &a, Layout2d layout, const void *src, void *
     }
 }
 
-// Output planes per 3D work item, chosen per launch: the run length r in
-// 1 .. max_run that minimises ceil(items(r) / slots) * (planes(r) + 2), the work
-// of the most loaded block slot (grid-stride rounds times the planes a work
-// item streams, its two halo planes included); ties go to the longer run.
-// Short runs spread small levels over the chip at the cost of reading their
-// halo planes again; long runs stream large levels with little re-reading.
-// With groups of 3 (the fp16 kernel's plane loop is unrolled three times),
-// a work item streams its planes in whole groups of three.
-int pick_zrun(int64_t tiles, int64_t depth, int64_t slots, bool groups_of_3, int max_run) {
-    int best = 1;
-    int64_t best_cost = INT64_MAX;
-    for (int r = 1; r <= max_run; ++r) {
-        const int64_t items = tiles * ((depth + r - 1) / r);
-        int64_t planes = std::min<int64_t>(r, depth) + 2;
-        if (groups_of_3) planes = (planes + 2) / 3 * 3;
-        const int64_t cost = (items + slots - 1) / slots * planes;
-        if (cost <= best_cost) {
-            best_cost = cost;
-            best = r;
-        }
-    }
-    return best;
-}
-
 template <typename T, int NIN, class Mlp>
 hipError_t launch_3d(const StepArgs &a, const void *src, void *dst, hipStream_t stream) {
-    constexpr bool kF16 = std::is_same_v<T, __half> && std::is_same_v<Mlp, MlpF16>;
-    const int tiles_x = (int)((a.ext.w + kTileW - 1) / kTileW);
-    const int tiles_y = (int)((a.ext.h + k3TY - 1) / k3TY);
-    const int64_t slots = (int64_t)device_cus() * (kF16 ? k3hBlocksPerCu : kBlocksPerCu);
-    const int zrun =
-        pick_zrun((int64_t)tiles_x * tiles_y, a.ext.d, slots, true, kF16 ? k3hZRun : k3ZRun);
-    const int64_t zruns = (a.ext.d + zrun - 1) / zrun;
-    const int64_t items = (int64_t)tiles_x * tiles_y * zruns;
-    if (items == 0) return hipSuccess;
-    if (items > INT32_MAX) return hipErrorInvalidValue;
-    if constexpr (kF16) {
-        const int grid = (int)std::min<int64_t>(items, slots);
-        auto kern = a.seg != nullptr
-                        ? (a.ext.w % 8 == 0 ? nca_step_mfma_3d_f16<NIN, true, false, true>
-                                            : nca_step_mfma_3d_f16<NIN, false, false, true>)
-                        : (a.ext.w % 8 == 0 ? nca_step_mfma_3d_f16<NIN, true, false>
-                                            : nca_step_mfma_3d_f16<NIN, false, false>);
-        kern<<<grid, kThreads, 0, stream>>>(
-            (const __half *)src, (__half *)dst, (int)a.ext.d, (int)a.ext.h, (int)a.ext.w, tiles_x,
-            tiles_y, (int)items, zrun, a.w.conv_w, a.w.conv_b, a.w.w1, a.w.b1, a.w.w2, a.level,
-            a.step, a.batch, a.seed, a.threshold, nullptr, 0, 0, 1, 1, 1, a.seg);
+    if constexpr (std::is_same_v<T, __half> && std::is_same_v<Mlp, MlpF16>) {
+        return launch_step_3d_f16(a, src, dst, nullptr, 0, 0, 1, 1, 1, stream);
     } else {
+        const int tiles_x = (int)((a.ext.w + kTileW - 1) / kTileW);
+        const int tiles_y = (int)((a.ext.h + k3TY - 1) / k3TY);
+        const int64_t slots = (int64_t)device_cus() * kBlocksPerCu;
+        const int zrun = pick_zrun((int64_t)tiles_x * tiles_y, a.ext.d, slots, 2, 3, k3ZRun);
+        const int64_t zruns = (a.ext.d + zrun - 1) / zrun;
+        const int64_t items = (int64_t)tiles_x * tiles_y * zruns;
+        if (items == 0) return hipSuccess;
+        if (items > INT32_MAX) return hipErrorInvalidValue;
         const int grid = (int)std::min<int64_t>(items, slots);
         auto kern = a.ext.w % 8 == 0 ? nca_step_mfma_3d<T, NIN, Mlp, true>
                                      : nca_step_mfma_3d<T, NIN, Mlp, false>;
@@ -1985,31 +1475,8 @@ hipError_t launch_3d(const StepArgs &a, const void *src, void *dst, hipStream_t 
             (const T *)src, (T *)dst, (int)a.ext.d, (int)a.ext.h, (int)a.ext.w, tiles_x, tiles_y,
             (int)items, zrun, a.w.conv_w, a.w.conv_b, a.w.w1, a.w.b1, a.w.w2, a.level, a.step,
             a.batch, a.seed, a.threshold);
+        return hipGetLastError();
     }
-    return hipGetLastError();
-}
-
-// fp16 3D first step fused with the upsample from the coarse state (planes of
-// cdh x cdw cells, factors fz, fy, fx) and the level's image img.
-template <int NIN>
-hipError_t launch_3d_f16_up(const StepArgs &a, const void *coarse, int cdh, int cdw, int fz,
-                            int fy, int fx, const void *img, void *dst, hipStream_t stream) {
-    const int tiles_x = (int)((a.ext.w + kTileW - 1) / kTileW);
-    const int tiles_y = (int)((a.ext.h + k3TY - 1) / k3TY);
-    const int64_t slots = (int64_t)device_cus() * k3hUpBlocksPerCu;
-    const int zrun = pick_zrun((int64_t)tiles_x * tiles_y, a.ext.d, slots, true, k3hZRun);
-    const int64_t zruns = (a.ext.d + zrun - 1) / zrun;
-    const int64_t items = (int64_t)tiles_x * tiles_y * zruns;
-    if (items == 0) return hipSuccess;
-    if (items > INT32_MAX) return hipErrorInvalidValue;
-    const int grid = (int)std::min<int64_t>(items, slots);
-    auto kern = a.ext.w % 8 == 0 ? nca_step_mfma_3d_f16<NIN, true, true>
-                                 : nca_step_mfma_3d_f16<NIN, false, true>;
-    kern<<<grid, kThreads, 0, stream>>>(
-        (const __half *)coarse, (__half *)dst, (int)a.ext.d, (int)a.ext.h, (int)a.ext.w, tiles_x,
-        tiles_y, (int)items, zrun, a.w.conv_w, a.w.conv_b, a.w.w1, a.w.b1, a.w.w2, a.level,
-        a.step, a.batch, a.seed, a.threshold, (const __half *)img, cdh, cdw, fz, fy, fx, nullptr);
-    return hipGetLastError();
 }
 
 template <typename T, class Mlp>
@@ -2088,15 +1555,8 @@ hipError_t launch_step_mfma_up(const StepArgs &a, Layout2d layout, const void *c
                                int coarse_h, int coarse_w, int fz, int fy, int fx,
                                const void *img, void *dst, hipStream_t stream) {
     if (!step_mfma_fuses_upsample(a, MfmaMlp::Default, layout)) return hipErrorInvalidValue;
-    if (a.ndim == 3) {
-        if (a.n_in == 1)
-            return launch_3d_f16_up<1>(a, coarse, coarse_h, coarse_w, fz, fy, fx, img, dst,
-                                       stream);
-        if (a.n_in == 3)
-            return launch_3d_f16_up<3>(a, coarse, coarse_h, coarse_w, fz, fy, fx, img, dst,
-                                       stream);
-        return hipErrorInvalidValue;
-    }
+    if (a.ndim == 3)
+        return launch_step_3d_f16(a, coarse, dst, img, coarse_h, coarse_w, fz, fy, fx, stream);
     if (is_c12(a) && a.dtype == Dtype::F16) {
         if (a.n_in == 1)
             return launch_rows<__half, 1, MlpC12h, true>(a, coarse, dst, img, coarse_w, fy, fx,
