@@ -38,8 +38,11 @@ constexpr int kQuadPlane = plane_stride(kRegionMax * kRegionMax);   // 16-byte w
 // Plans count the CUs of a full MI355X, not the device's, so that the launch
 // sequence is the same on every device.
 constexpr int64_t kPlanCus = 256;
-constexpr int64_t kBlockMaxCells = 400000;
-constexpr double kTurnUs = 1.05, kTapeTurnUs = 1.5;
+// Above these sizes one launch per step wins (one step at 724^2, fp32 then
+// fp16: 17.6 against 20.8 us, 14.7 against 18.1; 1001^2: 31.6 against 31.1,
+// 27.8 against 27.0), or, for the training tape, nothing larger was timed.
+constexpr int64_t kBlockMaxCells = 600000, kTapeMaxCells = 400000, kBlockMaxSide = 400000;
+constexpr double kTurnUs = 1.05, kTurnF16Us = 0.88, kTapeTurnUs = 1.5;
 
 struct BlockArgs {
     const void *src;      // the level's state; the coarse state with an upsample; unused for a seed
@@ -394,7 +397,7 @@ namespace {
 // Time model of the launches that run `steps` steps on T x T tiles, at most k
 // per launch, in us: 2.4 for a launch, and for each round of blocks (one block
 // per CU: its LDS) 2.8 until its first step (loads, weights, fire bits) and
-// one turn of 8 units per kTurn.  Measured, C = 16 fp32: 9.4 / 9.9 / 10.6 /
+// one turn of 8 units per kTurnUs (fp16 operands: kTurnF16Us).  Measured, C = 16 fp32: 9.4 / 9.9 / 10.6 /
 // 13.4 / 20.8 us for 5 steps of 16^2 (T 4), 16^2 (8), 128^2 (8), 4 of 256^2
 // (16), 5 of 320^2 (20); the model gives 10.5 / 10.5 / 10.5 / 12.6 / 19.9.
 constexpr double kLaunchUs = 2.4, kBlockUs = 2.8;
@@ -432,13 +435,16 @@ bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBl
     }
     // (the kernel's exact divisions need h, w < 2^19, its offsets 32 bits)
     const int64_t h = a.ext.h, w = a.ext.w;
-    if (h > kBlockMaxCells || w > kBlockMaxCells || h * w > kBlockMaxCells) return false;
-    const double turn_us = tape ? kTapeTurnUs : kTurnUs;
+    const int64_t max_cells = tape ? kTapeMaxCells : kBlockMaxCells;
+    if (h > kBlockMaxSide || w > kBlockMaxSide || h * w > max_cells) return false;
+    const double turn_us = tape ? kTapeTurnUs : a.dtype == Dtype::F16 ? kTurnF16Us : kTurnUs;
     // One launch per step on the row kernel, measured: 5.0 us up to 128^2
-    // cells, 6.8 at 256^2, 8.8 at 320^2, 11.3 at 512^2, 20.6 at 724^2, 27.7 at
-    // 1024^2 (the training forward about 1 us more).
-    // The images of a batch would run one after another there.
-    double best = (double)steps * images * ((tape ? 5.5 : 4.5) + (double)(h * w) / 45000.0);
+    // cells, 6.8 at 256^2, 8.8 at 320^2, 11.3 at 512^2, 27.7 at 1024^2; where
+    // rows do not start on 8-cell boundaries 14.3 at 600^2, 20.8 at 724^2
+    // (the training forward about 1 us more).  The images of a batch would run
+    // one after another there.
+    double best = (double)steps * images *
+                  ((tape ? 5.5 : 4.5) + (double)(h * w) / (w % 8 == 0 ? 45000.0 : 33000.0));
     bool use = false;
     for (int tile : {4, 6, 8, 10, 12, 14, 16, 18, 20, 22, 24, 28}) {
         if (tile > 4 && tile / 2 >= std::max(h, w)) break;

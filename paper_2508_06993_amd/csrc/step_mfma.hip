@@ -1338,7 +1338,7 @@ constexpr int kBlocksPerCu = 2;
 // latency of a wave's rows, not by throughput, and the extra halo rows of
 // short runs cost less than idle SIMDs.  Measured against 16 x 32 tiles:
 // medium 2D pass 1.43 -> 1.25 ms, tiny 2D 0.285 -> 0.22 ms, training step
-// 3.20 -> 3.07 ms; aiming at one run per wave slot (2 per SIMD) or at half a
+// 3.20 -> 3.07 ms; on those levels one run per wave slot (2 per SIMD) or half a
 // run per SIMD was slower.  The row kernel sums the taps in the tile
 // kernel's order, so the results are the same bits.  Two steps per launch
 // need at least one two-step run per wave slot (kPlanSlots).  Both counts are
@@ -1354,12 +1354,38 @@ struct RowsPlan {
     int64_t runs, items, slots;   // slots: wave slots of this device (grid size)
 };
 
+// From kLongRun rows a run, more and shorter runs pay: one wave a SIMD leaves
+// gaps that its one row in flight does not fill.  Two runs a SIMD do for fp16
+// states whose rows start on 8-cell boundaries and for fp32 states whose rows
+// do not (their fire draws take twice the lanes); three, the third of which a
+// SIMD's waves reach at different times, for fp16 states with such rows; fp32
+// states with aligned rows keep one.  Where runs would pass k2RunRows there
+// are as many per SIMD as it takes.  A count just above a multiple of the
+// SIMDs is the worst case, so runs grow until it is not.  Microseconds a step
+// with 1, 2, 3 runs a SIMD: fp16 724^2 19.6, 20.0, 18.1; 999 x 1337 37.7, 33.4,
+// 31.3; 1024^2 26.0, 24.0, 25.2; 1408 x 2048 61.7, 50.2, 49.4; fp32 800 x 900
+// 25.1, 23.5, 24.7; 999 x 1337 39.7, 38.3, 37.9; 1200 x 1500 51.2, 46.0, 47.6;
+// 1024^2 26.7, 29.0, 29.5; 1408 x 2048 74.2, 79.3, 76.2; 600^2 fp16 13.4, 14.1,
+// 14.8; 2816 x 2048 in runs of 128 rows (1408) 170 fp32, 127 fp16, with two
+// runs a SIMD 153, 103.
+constexpr int kLongRun = 17, kLongRunF32 = 20;
+
 RowsPlan rows_plan(const StepArgs &a) {
     RowsPlan r;
     r.tiles_x = (int)((a.ext.w + kTileW - 1) / kTileW);
     r.slots = (int64_t)device_cus() * 4 * k2WavesPerSimd;
-    r.run = (int)std::min<int64_t>(
-        k2RunRows, std::max<int64_t>(2, (a.ext.h * r.tiles_x + kRowRuns - 1) / kRowRuns));
+    const auto rows = [&](int64_t n) {   // rows of a run with n runs a SIMD
+        return std::max<int64_t>(2, (a.ext.h * r.tiles_x + n * kRowRuns - 1) / (n * kRowRuns));
+    };
+    const bool half = a.dtype == Dtype::F16, aligned = a.ext.w % 8 == 0;
+    int64_t run = rows(1);
+    if (run >= (half ? kLongRun : kLongRunF32)) {
+        int64_t n = 1 + (half ? 1 : 0) + (aligned ? 0 : 1);
+        n = std::max(n, (run + k2RunRows - 1) / k2RunRows);
+        run = rows(n);
+        while (run < k2RunRows && (a.ext.h + run - 1) / run * r.tiles_x > n * kRowRuns) ++run;
+    }
+    r.run = (int)std::min<int64_t>(k2RunRows, run);
     r.runs = (a.ext.h + r.run - 1) / r.run;
     r.items = (int64_t)r.tiles_x * r.runs;
     return r;

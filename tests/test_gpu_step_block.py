@@ -38,7 +38,7 @@ def _level(model, state, weights, steps, rate):
 
 @pytest.mark.parametrize("dtype,c,h", KINDS)
 @pytest.mark.parametrize("shape", [(1, 1), (3, 70), (16, 16), (33, 61), (64, 40), (130, 131),
-                                   (257, 250), (9, 2000)])
+                                   (257, 250), (9, 2000), (700, 851)])
 def test_levels_equal_single_steps(dtype, c, h, shape):
     n_in = 1 if shape[0] % 2 else 3
     wl = scaled(TINY_2D, (1,) + shape, channels=c, hidden=h, n_in=n_in, dtype=dtype, factors=(),
