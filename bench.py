@@ -115,14 +115,16 @@ def arithmetic_label(wl, kernel: str) -> str:
 
 
 STEP_SOURCES = ("paper_2508_06993_amd/csrc/step_mfma.hip",
+                "paper_2508_06993_amd/csrc/step_block.hip",
+                "paper_2508_06993_amd/csrc/step_3d_f16.hip",
                 "paper_2508_06993_amd/csrc/step_common.h",
                 "paper_2508_06993_amd/csrc/device_common.h")
 HOST_MARKER = "// ==== host side"
 
 
 def step_source_sha256() -> str:
-    """Hash of the step kernels' device code: device_common.h, step_common.h
-    and the part of step_mfma.hip before its host-side launch code."""
+    """Hash of the step kernels' device code: each of STEP_SOURCES, up to its
+    host-side launch code where that is marked."""
     import hashlib
     h = hashlib.sha256()
     for rel in STEP_SOURCES:

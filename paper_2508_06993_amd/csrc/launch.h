@@ -67,8 +67,8 @@ struct StepArgs {
     int hidden = kH;
     uint64_t seed;
     uint64_t threshold;
-    // Device [cells] uint8 or null: a two-step launch, or a single step of the
-    // fp16 3D kernel (see step_single_fuses_readout), also writes the
+    // Device [cells] uint8 or null: a two-step launch, or a single fp16 3D
+    // step (see step_single_fuses_readout), also writes the
     // two-class readout of the state it stores.
     uint8_t *seg = nullptr;
     KernelChoice kc;      // step kernel of the matrix-core / vector paths
@@ -177,7 +177,7 @@ bool step_mfma_serves(const StepArgs &a, Layout2d layout);
 hipError_t launch_step_mfma(const StepArgs &a, MfmaMlp mlp, Layout2d layout, const void *src,
                             void *dst, hipStream_t stream);
 // The first step of a level fused with the upsample + inject from the next
-// coarser level (2D row-streaming kernel and fp16 3D kernel, default operand
+// coarser level (2D row-streaming kernel and fp16 3D step, default operand
 // policy only):
 // step_mfma_fuses_upsample says whether launch_step_mfma would run that kernel
 // for `a`; launch_step_mfma_up then reads the coarse state (width coarse_w,
@@ -239,6 +239,7 @@ inline int pick_zrun(int64_t tiles, int64_t depth, int64_t slots, int extra, int
     }
     return best;
 }
+
 // The fp16 3D step of C = 16, H = 64 models with fp16 MLP operands
 // (step_3d_f16.hip); img null: src is a state of the level, else the first step
 // fused with the upsample from the coarse state src (planes of cdh x cdw cells).

@@ -120,8 +120,8 @@ __device__ __forceinline__ int gen_hidden(int p, int g, int s) {
 }
 
 // Blocks per CU (4 waves each) that LDS (160 KB per CU) and registers allow:
-// 2D C = 12 three (about 32 KB of LDS each), 2D C = 20 and 3D C = 12 two
-// (79 KB and 55 KB), 3D C = 20 one (115 KB).
+// 2D C = 12 three (31 KB of LDS each), 2D C = 20 and 3D C = 12 two (66 KB and
+// 54 KB), 3D C = 20 one (105 KB).
 template <int NDIM, int C>
 constexpr int kGenBlocksPerCu = NDIM == 2 ? (C <= 12 ? 3 : 2) : (C <= 12 ? 2 : 1);
 

@@ -1081,15 +1081,11 @@ __global__ __launch_bounds__(64, k2WavesPerSimd) void nca_step2_mfma_2d_rows(
 constexpr int k3TY = 8;
 // Longest run of output planes per work item.  A run re-reads two halo planes,
 // so long runs on deep levels stream less; its fire words (one evaluation per
-// 4 or 8 planes) take k3ZRun / 4 x 64 B of LDS per wave.  128 keeps the fp16
-// step at 3 blocks per CU (44 KB each) and the fp32 one at 2 (78 KB); against
-// 32 it took the video pass 89.0 -> 85.3 ms (64: 86.9 ms).  The fp16 step
-// takes runs of up to 256 planes (16 KB of fire words per block: 52 KB, still
-// 3 blocks per CU).
+// 4 or 8 planes) take k3ZRun / 4 x 64 B of LDS per wave.  128 keeps 2 blocks
+// per CU (78 KB each).
 constexpr int k3ZRun = 128;
 // Work item i of a 3D step is tile (tx, ty) of z run zr, with
 // i = (zr * tiles_y + ty) * tiles_x + tx.
-
 
 // ALIGNED: rows start on an 8-cell boundary (w % 8 == 0), which makes the
 // ballot and the bit offset of a lane's cells lane constants.
@@ -1425,9 +1421,9 @@ RowsPlan pair_plan(const StepArgs &a) {
 // The ablation's C = 12, H = 48 model (supplement S10) on the kernels of
 // C = 16: the 2D row kernels and the 3D step with an fp32 ring, the default
 // operands, the lanes of channel quad 3 and hidden tile 3 idle.  (fp16 3D: the
-// fp16-ring step would sum the perception in fp16, which these steps never
-// did.  On a 48 x 120 x 216 clip the fp32 ring took the finest level's step
-// from 105 us on the generic kernel to the figure beside launch_3d.)
+// step of C = 16 rounds taps and perception to fp16, which these steps never
+// did.  With the fp32 ring the finest level's step of a 48 x 120 x 216 clip
+// takes 47 us, on the generic kernel 105.)
 using MlpC12 = MlpF16SM<12, 48>;
 using MlpC12h = MlpF16M<12, 48>;
 bool is_c12(const StepArgs &a) { return a.channels == 12 && a.hidden == 48; }
