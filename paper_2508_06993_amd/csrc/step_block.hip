@@ -334,8 +334,9 @@ __global__ __launch_bounds__(kBlockThreads, 1) void nca_steps_block_2d(const Blo
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 const float m = (float)((uint32_t)bits[r] & 1u);
-                o[r] = make_float4(fmaf(m, up[r][0], f[r][0]), fmaf(m, up[r][1], f[r][1]),
-                                   fmaf(m, up[r][2], f[r][2]), fmaf(m, up[r][3], f[r][3]));
+                o[r] = make_float4(
+                    gated<Mlp>(m, up[r][0], f[r][0]), gated<Mlp>(m, up[r][1], f[r][1]),
+                    gated<Mlp>(m, up[r][2], f[r][2]), gated<Mlp>(m, up[r][3], f[r][3]));
                 if constexpr (sizeof(T) == 2) {          // stored precision between the steps
                     o[r].x = __half2float(__float2half_rn(o[r].x));
                     o[r].y = __half2float(__float2half_rn(o[r].y));

@@ -44,6 +44,7 @@ __device__ __forceinline__ void pin(V &x) {
 // element (16 round trips, about 5 us per launch, measured).
 // kPerceptionScale: the factor the kernel applies to the perception weights
 // and bias (features 4..7 arrive multiplied by it).
+// kSelectGate: how the fire gate is applied (gated() below).
 // ---------------------------------------------------------------------------
 
 // ReLU as an integer max on the float's bits: negative floats (sign bit set)
@@ -56,6 +57,7 @@ __device__ __forceinline__ float relu(float x) {
 struct MlpF32 {
     static constexpr int kChannels = kC, kHidden = kH;
     static constexpr float kPerceptionScale = 1.f;
+    static constexpr bool kSelectGate = false;
     float w1[4][8];   // [jt][kc] = W1[jt*16 + n][feature(kc, g)]
     v4f b1[4];        // [jt][i]  = b1[jt*16 + 4g + i]
     float w2[4][4];   // [jt][i]  = W2[n][jt*16 + 4g + i]   (n = output channel)
@@ -146,6 +148,7 @@ __device__ __forceinline__ void split_bf16(const v8f &x, v8bf &hi, v8bf &lo) {
 struct MlpBf16x3 {
     static constexpr int kChannels = kC, kHidden = kH;
     static constexpr float kPerceptionScale = 1.f;
+    static constexpr bool kSelectGate = false;
     v8bf w1h[4], w1l[4];   // [jt] slot s: W1[jt*16 + n][feature(s, g)]
     v4f b1[4];
     v8bf w2h[2], w2l[2];   // [p] slot s: W2[n][hidden(p, s, g)]
@@ -251,6 +254,9 @@ struct MlpF16M {
     static constexpr int kChannels = C, kHidden = H;
     static constexpr int NT = H / 16;   // hidden tiles computed (a smaller model: see MlpF16SM)
     static constexpr float kPerceptionScale = 1.f;
+    // 12 / 48: a cell that does not fire keeps its stored bits whatever its
+    // update is, as on the generic kernel, which serves its other layout
+    static constexpr bool kSelectGate = C != kC;
     v8h w1[NT];
     v4f b1[NT];
     v8h w2[2];
@@ -352,6 +358,7 @@ struct MlpF16SM {
     static constexpr int kChannels = C, kHidden = H;
     static constexpr int NT = H / 16;   // hidden tiles computed
     static constexpr float kPerceptionScale = kF16ActScale;
+    static constexpr bool kSelectGate = false;
     v8h w1h[NT], w1l[NT];   // [jt] slot s: W1[jt*16 + n][feature(s, g)], hi + lo
     v4f b1[NT];             // b1 * 2^-8
     v8h w2h[2], w2l[2];     // [p] slot s: 2^8 W2[n][hidden(p, s, g)], hi + lo
@@ -558,11 +565,22 @@ template <typename T, int C> struct CellChunk {
     }
 };
 
+// Residual update of a channel: m is 1 for a cell that fires and 0 for one that
+// does not.  The fma returns the state of a cell that does not fire for finite
+// u only (and +0 for a state of -0); with kSelectGate it is kept bit for bit
+// for any u.
+template <class Mlp>
+__device__ __forceinline__ float gated(float m, float u, float f) {
+    if constexpr (Mlp::kSelectGate)
+        return m != 0.f ? f + u : f;
+    else
+        return fmaf(m, u, f);
+}
+
 // Residual update and store of the lane's 4 channels (fp32 values, stored in
 // the storage type) through the tile's store descriptor; `off` is the byte
 // offset of the cell in it, or kOut for a cell outside the grid.  u is +0 for
-// the input channels (zero W2 rows) and m is 0 for a cell that does not
-// fire: then the fma returns the state bit for bit (u finite).
+// the input channels (zero W2 rows; u finite).
 __device__ __forceinline__ void store_quad(float *, Rsrc w, uint32_t off, int g, const v4f &v) {
     const v4u x = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
                    __float_as_uint(v[3])};
@@ -573,14 +591,14 @@ __device__ __forceinline__ void store_quad(__half *, Rsrc w, uint32_t off, int g
     __builtin_amdgcn_raw_buffer_store_b64(x, w, off == kOut ? kOut : off + 8u * g, 0, 0);
 }
 
-template <typename T>
+template <class Mlp, typename T>
 __device__ __forceinline__ void update_store(T *tag, Rsrc w, uint32_t off, int g, const float f[8],
                                              const v4f &u, float m) {   // m: 1 fires, 0 keeps
     v4f out;
-    out[0] = fmaf(m, u[0], f[0]);
-    out[1] = fmaf(m, u[1], f[1]);
-    out[2] = fmaf(m, u[2], f[2]);
-    out[3] = fmaf(m, u[3], f[3]);
+    out[0] = gated<Mlp>(m, u[0], f[0]);
+    out[1] = gated<Mlp>(m, u[1], f[1]);
+    out[2] = gated<Mlp>(m, u[2], f[2]);
+    out[3] = gated<Mlp>(m, u[3], f[3]);
     store_quad(tag, w, off, g, out);
 }
 

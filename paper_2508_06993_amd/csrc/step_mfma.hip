@@ -341,7 +341,7 @@ __global__ __launch_bounds__(kThreads, k2BlocksPerCu) void nca_step_mfma_2d(
             const uint64_t idx = (uint64_t)y * dw + x;
             const uint64_t row_b0 = ((uint64_t)y * dw + x0) >> 3;
             const uint32_t off = x < dw ? (uint32_t)ly * row_bytes + (uint32_t)x * kCellBytes : kOut;
-            update_store(dst, wr, off, g, f, u, fire.bit(slot0 + r, idx, row_b0));
+            update_store<Mlp>(dst, wr, off, g, f, u, fire.bit(slot0 + r, idx, row_b0));
 #pragma unroll
             for (int k = 0; k < 8; ++k) f[k] = fn[k];
             // keep the scheduler from interleaving whole groups (register pressure)
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(64, k2WavesPerSimd) void nca_step_mfma_2d_rows(
                     const uint64_t idx = (uint64_t)yc * dw + x;
                     fires = fire.bit(phase, idx, row_b0);
                 }
-                update_store(dst, wr, off, g, f[grp], u, fires);
+                update_store<Mlp>(dst, wr, off, g, f[grp], u, fires);
             }
             shift();
         };
@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(64, k2WavesPerSimd) void nca_step2_mfma_2d_rows(
                     __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(o[3] > o[2] ? 1 : 0), sr,
                                                          so, 0, 0);
                 } else {
-                    update_store(dst, wr, off, g, f[grp], u, m);
+                    update_store<Mlp>(dst, wr, off, g, f[grp], u, m);
                 }
             }
         };
@@ -1305,7 +1305,7 @@ __global__ __launch_bounds__(kThreads, 2) void nca_step_mfma_3d(
                     const uint64_t fw = fwe[idx & 7];
                     m = (fw >> ((slot0 + r) * opr + (int)((idx >> 3) - row_b0))) & 1 ? 1.f : 0.f;
                 }
-                update_store(dst, wr, offs[grp], g, f, u, m);
+                update_store<Mlp>(dst, wr, offs[grp], g, f, u, m);
                 __builtin_amdgcn_sched_barrier(0);
             }
 
