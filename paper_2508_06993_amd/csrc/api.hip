@@ -331,12 +331,13 @@ int octree_nca_run_level(const octnca_model *model, void *buf0, void *buf1, octn
     if (overlap(buf0, bytes, buf1, bytes)) return OCTNCA_EINVAL;
     // The number of launches has the parity of `steps`, so that the result is
     // in buf1 exactly when steps is odd, whichever kernels run: an even number
-    // of two-step launches (the rest one step each), or on small levels one
-    // launch more where the division over launches has the other parity.
+    // of two-step launches (the rest one step each), or on small levels the best
+    // division over launches among those of that parity.  (The best of all with
+    // a launch added ran two steps of 512^2 cells in 30 us, one launch per step
+    // in 21.)
     const StepArgs a = step_args(model, extent, weights, level, seed, threshold, 0);
     StepBlockPlan blocks;
-    if (step_block_plan(a, false, steps, 1, &blocks)) {
-        blocks.launches += (blocks.launches ^ steps) & 1;
+    if (step_block_plan(a, false, steps, 1, &blocks, true)) {
         st = run_block_steps(a, blocks, buf0, buf0, buf1, StepBlockInput{}, steps, nullptr,
                              (hipStream_t)stream);
         if (st) return st;

@@ -101,12 +101,15 @@ hipError_t launch_step_pair_up(const StepArgs &a, const void *coarse, int coarse
 // takes these launches, and how: `launches` of them, launch i running
 // steps / launches steps, one more for i < steps % launches, on tiles of
 // `tile` x `tile` cells.  tape: the training forward (split-bf16 operands).
+// same_parity: only plans whose number of launches is odd where `steps` is (for
+// a caller whose result has to be in one of two buffers).
 struct StepBlockPlan {
     int tile = 0;
     int launches = 0;
     int steps_of(int i, int steps) const { return steps / launches + (i < steps % launches); }
 };
-bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBlockPlan *plan);
+bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBlockPlan *plan,
+                     bool same_parity = false);
 // Where a launch's first state comes from: img null, a state of the level at
 // src; else the coarse state at src (width coarse_w, factors fy, fx) with the
 // level's image, or with src null the image and zero hidden channels.

@@ -423,7 +423,8 @@ double block_cost(int64_t h, int64_t w, int images, int steps, int tile, int lau
 
 }  // namespace
 
-bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBlockPlan *plan) {
+bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBlockPlan *plan,
+                     bool same_parity) {
     if (a.ndim != 2 || steps < 1) return false;
     if (tape) {
         if (a.dtype != Dtype::F32 || !is_size(a, 16, 64)) return false;
@@ -451,7 +452,8 @@ bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBl
         if (tile > 4 && tile / 2 >= std::max(h, w)) break;
         int last = 0;
         for (int k = std::min({(kRegionMax - tile) / 2, kBlockMaxSteps, steps}); k >= 1; --k) {
-            const int launches = (steps + k - 1) / k;
+            int launches = (steps + k - 1) / k;
+            if (same_parity) launches += (launches ^ steps) & 1;
             if (launches == last) continue;
             last = launches;
             const double c = block_cost(h, w, images, steps, tile, launches, turn_us);

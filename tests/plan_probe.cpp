@@ -1,0 +1,44 @@
+// Prints the launch plans of the library's host code, one line per query read
+// from stdin, for the tests of the plans.
+//   block <dtype> <c> <h> <rows> <cols> <steps> <images> <same_parity> -> use tile launches
+#include <cstdio>
+#include <cstring>
+
+#include "launch.h"
+
+using namespace octnca;
+
+namespace {
+
+StepArgs args(const char *dtype, int ndim, int c, int h, long d, long rows, long cols) {
+    StepArgs a{};
+    a.dtype = std::strcmp(dtype, "f16") ? Dtype::F32 : Dtype::F16;
+    a.ndim = ndim;
+    a.n_in = 3;
+    a.ext = Extent3{d, rows, cols};
+    a.channels = c;
+    a.hidden = h;
+    return a;
+}
+
+}  // namespace
+
+int main() {
+    char what[16], dtype[8];
+    while (std::scanf("%15s", what) == 1) {
+        if (!std::strcmp(what, "block")) {
+            int c, h, steps, images, parity;
+            long rows, cols;
+            if (std::scanf("%7s %d %d %ld %ld %d %d %d", dtype, &c, &h, &rows, &cols, &steps,
+                           &images, &parity) != 8)
+                return 1;
+            StepBlockPlan p;
+            const bool use = step_block_plan(args(dtype, 2, c, h, 1, rows, cols), false, steps,
+                                             images, &p, parity != 0);
+            std::printf("%d %d %d\n", use ? 1 : 0, use ? p.tile : 0, use ? p.launches : 0);
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}

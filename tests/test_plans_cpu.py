@@ -1,0 +1,47 @@
+"""How the library's host code divides steps over launches (no GPU): the plans
+are printed by a small host program linked against the built library."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2508_06993_amd.build import CSRC, INCLUDE, LIB_NAME, PKG, hipcc
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def plans(library_path, tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plans") / "plan_probe")
+    subprocess.run([hipcc(), "-std=c++17", "-O1", "-x", "hip", "--offload-host-only", "-I", INCLUDE,
+                    "-I", CSRC, os.path.join(HERE, "plan_probe.cpp"), "-o", exe, "-L", PKG,
+                    "-l:" + LIB_NAME, "-Wl,-rpath," + PKG], check=True)
+
+    def ask(queries):
+        text = "\n".join(" ".join(str(v) for v in q) for q in queries)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        rows = [tuple(int(v) for v in line.split()) for line in out.splitlines()]
+        assert len(rows) == len(queries)
+        return rows
+    return ask
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("c,h", [(16, 64), (12, 48)])
+def test_plans_of_a_given_parity(plans, dtype, c, h):
+    """A run whose result has to be in one of two buffers takes the best plan
+    among those with the parity of its steps: two launches of one step each are
+    not used where one launch of one step is not."""
+    sizes = [(1, 1), (64, 64), (128, 128), (320, 320), (512, 512), (600, 600), (700, 851),
+             (774, 775), (40, 6000), (6000, 40), (333, 1001)]
+    ask = lambda steps, parity: plans([("block", dtype, c, h, *s, steps, 1, parity) for s in sizes])
+    one = ask(1, 0)
+    for steps in (1, 2, 3, 4, 5, 8, 19, 20, 23):
+        for free, same, single in zip(ask(steps, 0), ask(steps, 1), one):
+            if same[0]:
+                assert free[0]
+                assert same[2] % 2 == steps % 2 and same[2] >= free[2] - 1
+            if free[0] and free[2] % 2 == steps % 2:
+                assert same == free
+            if steps == 2:
+                assert same[0] == single[0]
