@@ -680,6 +680,12 @@ int64_t blocks_of(const StepArgs &a, int64_t tiles) {
 // 26.0 (25.3); 40^2 with T 8, k 4: 8.2 (9.2), T 8, k 1: 14.1 (15.6).
 constexpr double kBwLaunchUs = 7.5, kBwTileUs = 4.0, kBwStepUs = 1.6, kBwOwnUs = 2.45,
                  kBwRingUs = 1.5;
+// A single 2D step below this size is faster on 64-cell blocks, which need not
+// copy the weights and add up waves (a step's backward with its last two
+// kernels, 64-cell blocks against these tiles: 33 x 61 cells 23.0 and 25.7 us,
+// 100 x 128 24.3 and 27.1, 160^2 27.9 and 28.9, 200 x 220 38.0 and 36.4, 256^2
+// 42.0 and 36.0, 320^2 62.0 and 45.3); two steps and more are not.
+constexpr int64_t kBw2dOneStep = 32000;
 // 3D levels from this size on take the tiles of 4 x 8 x 8: 12 x 96 x 96 cells
 // 68 -> 51 us a step; 12 x 48 x 48 would go from 22 to 28.
 constexpr int64_t kBw3dCells = 60000;
@@ -716,6 +722,7 @@ bool bwd_block_plan(const StepArgs &a, int steps, int64_t max_blocks, BwdBlockPl
         plan->launches = steps;
         return true;
     }
+    if (steps == 1 && a.ext.cells() < kBw2dOneStep) return false;
     double best = 1e30;
     plan->launches = 0;
     for (int tile : {6, 8, 10, 12, 14, 16, 18, 20, 22}) {

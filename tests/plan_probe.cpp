@@ -1,6 +1,7 @@
 // Prints the launch plans of the library's host code, one line per query read
 // from stdin, for the tests of the plans.
 //   block <dtype> <c> <h> <rows> <cols> <steps> <images> <same_parity> -> use tile launches
+//   bwd <ndim> <d> <rows> <cols> <steps> -> use tile launches
 #include <cstdio>
 #include <cstring>
 
@@ -35,6 +36,14 @@ int main() {
             StepBlockPlan p;
             const bool use = step_block_plan(args(dtype, 2, c, h, 1, rows, cols), false, steps,
                                              images, &p, parity != 0);
+            std::printf("%d %d %d\n", use ? 1 : 0, use ? p.tile : 0, use ? p.launches : 0);
+        } else if (!std::strcmp(what, "bwd")) {
+            int ndim, steps;
+            long d, rows, cols;
+            if (std::scanf("%d %ld %ld %ld %d", &ndim, &d, &rows, &cols, &steps) != 5) return 1;
+            BwdBlockPlan p;
+            const bool use = bwd_block_plan(args("f32", ndim, 16, 64, d, rows, cols), steps,
+                                            int64_t(1) << 30, &p);
             std::printf("%d %d %d\n", use ? 1 : 0, use ? p.tile : 0, use ? p.launches : 0);
         } else {
             return 1;

@@ -40,6 +40,13 @@ def test_step_matches_oracle(gpu, ndim, n_in, shape):
             <= TOL_WEIGHT, k
 
 
+@pytest.mark.parametrize("n_in,shape", [(3, (1, 179, 181)), (1, (1, 2, 16100)), (3, (1, 11000, 3))])
+def test_2d_step_past_the_one_step_line(gpu, n_in, shape):
+    """Single steps take the large tiles from 32000 cells on: thin and ragged
+    ones of that size."""
+    test_step_matches_oracle(gpu, 2, n_in, shape)
+
+
 @pytest.mark.parametrize("ndim,n_in,shape,steps,rate", [
     (2, 3, (1, 20, 20), 20, 0.5), (2, 1, (1, 61, 45), 7, 1.0), (2, 3, (1, 170, 150), 5, 0.5),
     (2, 3, (1, 321, 318), 3, 0.4), (2, 3, (1, 9, 32), 4, 0.5), (2, 3, (1, 1, 40), 3, 0.5),

@@ -45,3 +45,11 @@ def test_plans_of_a_given_parity(plans, dtype, c, h):
                 assert same == free
             if steps == 2:
                 assert same[0] == single[0]
+
+
+@pytest.mark.parametrize("rows,cols,steps,large", [
+    (33, 61, 1, 0), (100, 128, 1, 0), (160, 160, 1, 0), (200, 220, 1, 1), (320, 320, 1, 1),
+    (33, 61, 2, 1), (20, 20, 20, 1), (1, 1, 3, 1)])
+def test_2d_backward_on_large_tiles(plans, rows, cols, steps, large):
+    """One step of a small level runs on 64-cell blocks, where it is faster."""
+    assert plans([("bwd", 2, 1, rows, cols, steps)])[0][0] == large
