@@ -686,9 +686,17 @@ constexpr double kBwLaunchUs = 7.5, kBwTileUs = 4.0, kBwStepUs = 1.6, kBwOwnUs =
 // 100 x 128 24.3 and 27.1, 160^2 27.9 and 28.9, 200 x 220 38.0 and 36.4, 256^2
 // 42.0 and 36.0, 320^2 62.0 and 45.3); two steps and more are not.
 constexpr int64_t kBw2dOneStep = 32000;
-// 3D levels from this size on take the tiles of 4 x 8 x 8: 12 x 96 x 96 cells
-// 68 -> 51 us a step; 12 x 48 x 48 would go from 22 to 28.
-constexpr int64_t kBw3dCells = 60000;
+// 3D levels take the tiles of 4 x 8 x 8 where a round of one block per CU has at
+// least this many cells of its 65536 on average.  A round costs the same however
+// full its tiles are (one plane of cells fills a quarter of a tile), 64-cell
+// blocks cost by the cell.  A step of a ten-step training call, 64-cell blocks
+// against these tiles, us: one round, 12 x 48 x 48 cells 36 and 44, 8 x 64 x 64
+// 36 and 44, 16 x 48 x 48 45.8 and 45.1, 10 x 64 x 64 45.4 and 44.1, 24 x 48 x
+// 48 57 and 51, 4 x 128 x 128 54 and 46; two, 5 x 96 x 96 53 and 61, 6 x 112 x
+// 112 68.5 and 67.3, 3 x 160 x 160 83 and 67, 12 x 96 x 96 86 and 71; three, 2 x
+// 200 x 200 67 and 81, 7 x 131 x 129 109 and 95; four, 256 x 256 85 and 91, 24 x
+// 96 x 96 152 and 118; ten, 24 x 160 x 160 410 and 266.
+constexpr int64_t kBw3dRoundCells = 36000;
 
 double bwd_cost(int64_t h, int64_t w, int steps, int tile, int launches) {
     const int64_t tiles = (h + tile - 1) / tile * ((w + tile - 1) / tile);
@@ -716,8 +724,9 @@ bool bwd_block_plan(const StepArgs &a, int steps, int64_t max_blocks, BwdBlockPl
     // 32-bit byte offsets into a state
     if (a.ext.cells() > (int64_t(1) << 32) / 64 - 1) return false;
     if (a.ndim == 3) {
-        // Small 3D levels are faster on 64-cell blocks: few tiles leave CUs idle.
-        if (a.ext.cells() < kBw3dCells || blocks_of(a, tiles_of(a, 8)) > max_blocks) return false;
+        const int64_t tiles = tiles_of(a, 8), rounds = (tiles + kPlanCus - 1) / kPlanCus;
+        if (a.ext.cells() < kBw3dRoundCells * rounds || blocks_of(a, tiles) > max_blocks)
+            return false;
         plan->tile = 8;
         plan->launches = steps;
         return true;

@@ -47,6 +47,17 @@ def test_2d_step_past_the_one_step_line(gpu, n_in, shape):
     test_step_matches_oracle(gpu, 2, n_in, shape)
 
 
+@pytest.mark.parametrize("n_in,shape", [(1, (11, 60, 61)), (3, (4, 143, 133)), (1, (12, 80, 77))])
+def test_3d_step_on_large_tiles(gpu, n_in, shape):
+    """Ragged volumes that fill the 4 x 8 x 8 tiles well enough to take them:
+    fewer tiles than CUs, more."""
+    test_step_matches_oracle(gpu, 3, n_in, shape)
+
+
+def test_3d_level_on_large_tiles(gpu):
+    test_level_equals_its_steps(gpu, 3, 1, (11, 90, 84), 3, 0.5)
+
+
 @pytest.mark.parametrize("ndim,n_in,shape,steps,rate", [
     (2, 3, (1, 20, 20), 20, 0.5), (2, 1, (1, 61, 45), 7, 1.0), (2, 3, (1, 170, 150), 5, 0.5),
     (2, 3, (1, 321, 318), 3, 0.4), (2, 3, (1, 9, 32), 4, 0.5), (2, 3, (1, 1, 40), 3, 0.5),

@@ -53,3 +53,14 @@ def test_plans_of_a_given_parity(plans, dtype, c, h):
 def test_2d_backward_on_large_tiles(plans, rows, cols, steps, large):
     """One step of a small level runs on 64-cell blocks, where it is faster."""
     assert plans([("bwd", 2, 1, rows, cols, steps)])[0][0] == large
+
+
+@pytest.mark.parametrize("d,rows,cols,large", [
+    (12, 48, 48, 0), (8, 64, 64, 0), (16, 48, 48, 1), (24, 48, 48, 1), (4, 128, 128, 1),
+    (5, 96, 96, 0), (6, 112, 112, 1), (12, 96, 96, 1), (2, 200, 200, 0), (1, 256, 256, 0),
+    (2, 400, 400, 0), (7, 131, 129, 1), (24, 160, 160, 1)])
+def test_3d_backward_on_large_tiles(plans, d, rows, cols, large):
+    """The tiles are 4 planes deep: thin volumes leave them mostly empty and run
+    on 64-cell blocks, as do volumes that leave most CUs idle."""
+    for steps in (1, 4):
+        assert plans([("bwd", 3, d, rows, cols, steps)])[0][0] == large
