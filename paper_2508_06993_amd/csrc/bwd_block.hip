@@ -664,11 +664,20 @@ int64_t tiles_of(const StepArgs &a, int tile) {
     return (a.ext.h + tile - 1) / tile * ((a.ext.w + tile - 1) / tile);
 }
 // Blocks of a launch: in 3D the tiles divided evenly over as few rounds as one
-// block per CU of a full MI355X gives.
+// block per CU of a full MI355X gives.  A block adds up its tiles' weight
+// gradients in fp32 (the rows are added in fp64), so from kBw3dTiles tiles a
+// block on the launch is that many blocks per CU, one after another.  With all
+// tiles of a CU in one sum (38 of them in 24 x 320 x 320 cells, 100 in 40 x 400
+// x 400), the gradients of states of one sign were 1 to 4% further from 64 bits
+// than those of 64-cell blocks (dconv_w 1.60e-7 and 1.55e-7), with at most eight
+// they are as near.
+constexpr int64_t kBw3dTiles = 8;
 int64_t blocks_of(const StepArgs &a, int64_t tiles) {
     if (a.ndim == 2) return tiles;
     const int64_t rounds = (tiles + kPlanCus - 1) / kPlanCus;
-    return (tiles + rounds - 1) / rounds;
+    const int64_t sums = (rounds + kBw3dTiles - 1) / kBw3dTiles;   // blocks per CU
+    const int64_t per_block = (rounds + sums - 1) / sums;
+    return (tiles + per_block - 1) / per_block;
 }
 
 // Time model of a 2D level's launches on T x T tiles, in us: a launch with its

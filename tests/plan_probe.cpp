@@ -1,7 +1,7 @@
 // Prints the launch plans of the library's host code, one line per query read
 // from stdin, for the tests of the plans.
 //   block <dtype> <c> <h> <rows> <cols> <steps> <images> <same_parity> -> use tile launches
-//   bwd <ndim> <d> <rows> <cols> <steps> -> use tile launches
+//   bwd <ndim> <d> <rows> <cols> <steps> -> use tile launches rows (of gradient sums)
 #include <cstdio>
 #include <cstring>
 
@@ -44,7 +44,9 @@ int main() {
             BwdBlockPlan p;
             const bool use = bwd_block_plan(args("f32", ndim, 16, 64, d, rows, cols), steps,
                                             int64_t(1) << 30, &p);
-            std::printf("%d %d %d\n", use ? 1 : 0, use ? p.tile : 0, use ? p.launches : 0);
+            const StepArgs a = args("f32", ndim, 16, 64, d, rows, cols);
+            std::printf("%d %d %d %lld\n", use ? 1 : 0, use ? p.tile : 0, use ? p.launches : 0,
+                        use ? (long long)bwd_block_rows(a, p) : 0ll);
         } else {
             return 1;
         }

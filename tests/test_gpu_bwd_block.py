@@ -58,6 +58,43 @@ def test_3d_level_on_large_tiles(gpu):
     test_level_equals_its_steps(gpu, 3, 1, (11, 90, 84), 3, 0.5)
 
 
+def test_3d_sums_over_many_tiles(gpu):
+    """Weight gradients of a volume of 40000 tiles whose terms have one sign (no
+    cancellation: a long fp32 sum shows its error): every cell fires, every
+    hidden unit is active, so the sums are linear in G' and their fp64 values
+    follow from those of G' and G' S^T.  The result's own rounding to fp32 is up
+    to 2^-24 of it.  What the sums add: a row's 2048 cells, 4 a product and 8
+    waves apart, are some 64 roundings of up to 2^-25 each, sqrt(64) * 2^-25 =
+    2^-22 a row, and the 5000 rows are added in fp64: 2^-22 / sqrt(5000) = 2^-28."""
+    shape = (64, 400, 400)
+    rng = np.random.default_rng(5)
+    w = rand_weights(rng, 3)
+    for k in KEYS:
+        setattr(w, k, np.abs(getattr(w, k)) * 0.1)
+    state = torch.rand(shape + (C,), device="cuda", generator=torch.Generator("cuda").manual_seed(4))
+    g_out = torch.rand(shape + (C,), device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    model = octnca.Model(ndim=3, n_in=1)
+    ws = torch.empty(octnca.octree_nca_step_backward_workspace_bytes(model, shape),
+                     dtype=torch.uint8, device="cuda")
+    grads, gin = zero_grads(w), torch.empty_like(g_out)
+    octnca.octree_nca_step_backward(model, state, g_out, upload_weights([w])[0], 0, 0, 1.0, 1, gin,
+                                    grads, ws)
+    # per cell gu = G' (hidden channels), ga = W2^T gu, gP = (W1^T ga)_perception
+    w1, w2 = (torch.from_numpy(v).cuda().double() for v in (w.w1, w.w2))
+    gu = g_out.double()
+    gu[..., :1] = 0
+    gu_sum = gu.reshape(-1, C).sum(0)
+    ga_sum = w2.T @ gu_sum
+    want = {"b1": ga_sum, "conv_b": (w1.T @ ga_sum)[C:]}
+    # dW1's state columns: sum of ga S^T
+    f = state.double().reshape(-1, C)
+    want_w1 = w2.T @ (gu.reshape(-1, C).T @ f)
+    torch.cuda.synchronize()
+    for k, v in want.items():
+        assert max_rel_err(to_np(grads[k]), to_np(v)) <= 2.0 ** -24 + 2.0 ** -28, k
+    assert max_rel_err(to_np(grads["w1"])[:, :C], to_np(want_w1)) <= 2.0 ** -24 + 2.0 ** -28
+
+
 @pytest.mark.parametrize("ndim,n_in,shape,steps,rate", [
     (2, 3, (1, 20, 20), 20, 0.5), (2, 1, (1, 61, 45), 7, 1.0), (2, 3, (1, 170, 150), 5, 0.5),
     (2, 3, (1, 321, 318), 3, 0.4), (2, 3, (1, 9, 32), 4, 0.5), (2, 3, (1, 1, 40), 3, 0.5),

@@ -64,3 +64,13 @@ def test_3d_backward_on_large_tiles(plans, d, rows, cols, large):
     on 64-cell blocks, as do volumes that leave most CUs idle."""
     for steps in (1, 4):
         assert plans([("bwd", 3, d, rows, cols, steps)])[0][0] == large
+
+
+@pytest.mark.parametrize("d,rows,cols", [(12, 96, 96), (24, 160, 160), (24, 320, 320),
+                                         (40, 400, 400), (101, 203, 307)])
+def test_3d_backward_sums_few_tiles_in_fp32(plans, d, rows, cols):
+    """A row of weight-gradient sums, kept in fp32, covers at most 8 tiles of 256
+    cells however large the volume is; the rows are added in fp64."""
+    tiles = -(-d // 4) * -(-rows // 8) * -(-cols // 8)
+    use, _, _, sums = plans([("bwd", 3, d, rows, cols, 1)])[0]
+    assert use and tiles <= 8 * sums and sums <= tiles
