@@ -58,6 +58,8 @@ constexpr int kPQuad = kTY * kPRow;
 constexpr int kEvals = 32;                  // fire evaluations of a run
 constexpr int kMaxRun = kEvals * 8;         // planes of a run (rows 8-aligned; else half)
 constexpr int kBlocksPerCu3 = 2;
+// a channel's taps in LDS: planes of 9 on even halves, then the bias
+constexpr int kTapPlane = 10, kBias = 3 * kTapPlane, kTaps = kBias + 2;
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float v2f_ __attribute__((ext_vector_type(2)));
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
     __shared__ __align__(16) _Float16 ring[4][kPlane];       // plane z in slot z & 3
     __shared__ __align__(16) uint2 pbuf[2][4 * kPQuad];      // perception of plane z in z & 1
     __shared__ uint64_t fire_words[4][kEvals][8];
-    __shared__ _Float16 cw[kC][28];                          // taps, bias
+    __shared__ __align__(4) _Float16 cw[kC][kTaps];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -106,7 +108,8 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
 
     for (int i = threadIdx.x; i < kC * 28; i += kThreads3) {
         const int c = i / 28, t = i % 28;
-        cw[c][t] = (_Float16)(t < 27 ? A.conv_w[c * 27 + t] : A.conv_b[c]);
+        cw[c][t < 27 ? t / 9 * kTapPlane + t % 9 : kBias] =
+            (_Float16)(t < 27 ? A.conv_w[c * 27 + t] : A.conv_b[c]);
     }
     MlpF16 mlp;
     mlp.load(A.w1, A.b1, A.w2, n, g, NIN);
@@ -127,9 +130,9 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
                 const int r = g - oy;                        // dy + 1
                 const int rc = min(max(r, 0), 2);
                 const _Float16 z = (_Float16)0.f;
-                const _Float16 w0 = r == rc ? w[m * 9 + 3 * rc] : z;
-                const _Float16 w1 = r == rc ? w[m * 9 + 3 * rc + 1] : z;
-                const _Float16 w2 = r == rc ? w[m * 9 + 3 * rc + 2] : z;
+                const _Float16 w0 = r == rc ? w[m * kTapPlane + 3 * rc] : z;
+                const _Float16 w1 = r == rc ? w[m * kTapPlane + 3 * rc + 1] : z;
+                const _Float16 w2 = r == rc ? w[m * kTapPlane + 3 * rc + 2] : z;
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
                     am[q][m][j] = j == ox ? w0 : j == ox + 1 ? w1 : j == ox + 2 ? w2 : z;
@@ -138,9 +141,9 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
             for (int j = 0; j < 8; ++j) {
                 const int r = g - oy, d = 8 + j % 2 - ox;
                 const bool ok = j < 6 && r >= 0 && r <= 2 && d <= 2;
-                const int at = min(j / 2, 2) * 9 + min(max(r, 0), 2) * 3 + min(d, 2);
+                const int at = min(j / 2, 2) * kTapPlane + min(max(r, 0), 2) * 3 + min(d, 2);
                 const _Float16 v = w[at];
-                am[q][3][j] = ok ? v : (g == 0 && j == 6) ? w[27] : (_Float16)0.f;
+                am[q][3][j] = ok ? v : (g == 0 && j == 6) ? w[kBias] : (_Float16)0.f;
             }
         }
 #pragma unroll
@@ -319,33 +322,86 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
         *reinterpret_cast<uint4 *>(out + 2) = make_uint4(o[2][0], o[2][1], o[3][0], o[3][1]);
         return (float)bad[0] == 0.f && (float)bad[1] == 0.f;
     };
-    // Some input or sum of plane z is not finite: tap by tap, each output from
-    // its own 27 cells, the lane's four neighbouring outputs together (a row of
-    // taps reads six cells at once; a 48 x 120 x 216 level of diverged states
-    // takes 108 us a step, one read at a time 516, finite states 37).
+    // Some input or sum of plane z is not finite: the wave's channels again, each
+    // output from its own 27 cells.  Lane (n, g) takes channel g of the wave's and
+    // all of block n, so a row of its window is two reads and serves two rows of
+    // outputs (two taps a dot product of fp16 values, fp32 sums); the four lanes
+    // of a block then exchange halves for the usual writes.  A 48 x 120 x 216
+    // level of diverged states takes 58 us a step (131 with four neighbouring
+    // cells a lane and a read per tap and cell: bound by those reads), finite
+    // states, and one infinite cell among them, 34.
     auto perceive_exact = [&](int z) {
-        _Float16 *o16 = reinterpret_cast<_Float16 *>(pbuf[z & 1] + wave * kPQuad + p_at);
-        const int y = 2 * by + (g >> 1), x = 8 * bx + 4 * (g & 1);   // the first tap
+        // addresses from here: hoisted, they would hold registers of the plane loop
+        int nn = n, gg = g;
+        pin(nn);
+        pin(gg);
+        const int c = 4 * wave + gg, y = 2 * (nn >> 2), x = 8 * (nn & 3);
+        const int body = c * kChan + y * kRow + x, tail = c * kChan + lds_at(y, x + 8);
+        const int tail_row = x + 8 < 32 ? kRow : 2;
+        float sum[2][8];
+#pragma unroll
+        for (int oy = 0; oy < 2; ++oy)
+#pragma unroll
+            for (int ox = 0; ox < 8; ++ox) sum[oy][ox] = (float)cw[c][kBias];
 #pragma unroll 1
-        for (int i = 0; i < 4; ++i) {
-            const int c = 4 * wave + i;
-            float sum[4];
+        for (int m = 0; m < 3; ++m) {
+            const _Float16 *pl = ring[(z + m + 3) & 3];
+            uint4 v8[4];
+            uint32_t v2[4], w[5];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) sum[k] = (float)cw[c][27];
-#pragma unroll 1
-            for (int t = 0; t < 27; t += 3) {
-                float v[6];
+            for (int i = 0; i < 5; ++i)
+                w[i] = reinterpret_cast<const uint32_t *>(cw[c] + m * kTapPlane)[i];
 #pragma unroll
-                for (int j = 0; j < 6; ++j)
-                    v[j] = (float)ring[(z + t / 9 - 1) & 3][c * kChan + lds_at(y + t % 9 / 3, x + j)];
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) sum[k] = fmaf((float)cw[c][t + dx], v[k + dx], sum[k]);
+            for (int r = 0; r < 4; ++r) {
+                v8[r] = *reinterpret_cast<const uint4 *>(pl + body + r * kRow);
+                v2[r] = *reinterpret_cast<const uint32_t *>(pl + tail + r * tail_row);
             }
+            // taps 0 and 1 of a row, and tap 2
+            const uint32_t w01[3] = {w[0], __builtin_amdgcn_alignbyte(w[2], w[1], 2), w[3]};
+            const float w2[3] = {(float)as_h2(w[1])[0], (float)as_h2(w[2])[1], (float)as_h2(w[4])[0]};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) o16[4 * k + i] = (_Float16)sum[k];
+            for (int r = 0; r < 4; ++r) {
+                // cells 2 i, 2 i + 1 and 2 i + 1, 2 i + 2 of the row
+                const uint32_t even[5] = {v8[r].x, v8[r].y, v8[r].z, v8[r].w, v2[r]};
+                uint32_t odd[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) odd[i] = __builtin_amdgcn_alignbyte(even[i + 1], even[i], 2);
+#pragma unroll
+                for (int oy = 0; oy < 2; ++oy) {
+                    const int dy = r - oy;
+                    if (dy < 0 || dy > 2) continue;
+#pragma unroll
+                    for (int ox = 0; ox < 8; ++ox) {
+                        const uint32_t v01 = ox & 1 ? odd[ox / 2] : even[ox / 2];
+                        sum[oy][ox] = __builtin_amdgcn_fdot2(as_h2(w01[dy]), as_h2(v01), sum[oy][ox], false);
+                        sum[oy][ox] = fmaf(w2[dy], (float)as_h2(even[ox / 2 + 1])[ox & 1], sum[oy][ox]);
+                    }
+                }
+            }
         }
+        // lane g: channel g of cells 4 q .. 4 q + 3 (q = 0 .. 3) -> channels 0 .. 3 of
+        // cells 4 g .. 4 g + 3, two cells a word
+        uint32_t o[4][2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            uint32_t q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float *f = &sum[i >> 1][4 * (i & 1) + 2 * k];
+                q[i] = as_u32(__builtin_convertvector(v2f_{f[0], f[1]}, h2));
+            }
+            const auto a = __builtin_amdgcn_permlane32_swap(q[0], q[2], false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(q[1], q[3], false, false);
+            const auto c01 = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+            const auto c23 = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+            o[2 * k][0] = __builtin_amdgcn_perm(c01[1], c01[0], 0x05040100u);
+            o[2 * k][1] = __builtin_amdgcn_perm(c23[1], c23[0], 0x05040100u);
+            o[2 * k + 1][0] = __builtin_amdgcn_perm(c01[1], c01[0], 0x07060302u);
+            o[2 * k + 1][1] = __builtin_amdgcn_perm(c23[1], c23[0], 0x07060302u);
+        }
+        uint2 *out = pbuf[z & 1] + wave * kPQuad + (y + (gg >> 1)) * kPRow + x + 4 * (gg & 1);
+        *reinterpret_cast<uint4 *>(out) = make_uint4(o[0][0], o[0][1], o[1][0], o[1][1]);
+        *reinterpret_cast<uint4 *>(out + 2) = make_uint4(o[2][0], o[2][1], o[3][0], o[3][1]);
     };
 
     const int64_t span = ((int64_t)A.items + gridDim.x - 1) / gridDim.x * gridDim.x;
