@@ -58,8 +58,8 @@ constexpr int kPQuad = kTY * kPRow;
 constexpr int kEvals = 32;                  // fire evaluations of a run
 constexpr int kMaxRun = kEvals * 8;         // planes of a run (rows 8-aligned; else half)
 constexpr int kBlocksPerCu3 = 2;
-// a channel's taps in LDS: planes of 9 on even halves, then the bias
-constexpr int kTapPlane = 10, kBias = 3 * kTapPlane, kTaps = kBias + 2;
+// a channel's taps in LDS: nine rows of three taps and a zero, then the bias
+constexpr int kBias = 9 * 4, kTaps = kBias + 4;
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float v2f_ __attribute__((ext_vector_type(2)));
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
     __shared__ __align__(16) _Float16 ring[4][kPlane];       // plane z in slot z & 3
     __shared__ __align__(16) uint2 pbuf[2][4 * kPQuad];      // perception of plane z in z & 1
     __shared__ uint64_t fire_words[4][kEvals][8];
-    __shared__ __align__(4) _Float16 cw[kC][kTaps];
+    __shared__ __align__(8) _Float16 cw[kC][kTaps];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -106,10 +106,10 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
     const int g = lane >> 4;
     const int dd = A.dd, dh = A.dh, dw = A.dw;
 
-    for (int i = threadIdx.x; i < kC * 28; i += kThreads3) {
-        const int c = i / 28, t = i % 28;
-        cw[c][t < 27 ? t / 9 * kTapPlane + t % 9 : kBias] =
-            (_Float16)(t < 27 ? A.conv_w[c * 27 + t] : A.conv_b[c]);
+    for (int i = threadIdx.x; i < kC * kTaps; i += kThreads3) {
+        const int c = i / kTaps, t = i % kTaps, tap = t / 4 * 3 + t % 4;
+        const float v = *(t < kBias ? A.conv_w + c * 27 + min(tap, 26) : A.conv_b + c);
+        cw[c][t] = (_Float16)(t % 4 < 3 ? v : 0.f);
     }
     MlpF16 mlp;
     mlp.load(A.w1, A.b1, A.w2, n, g, NIN);
@@ -118,33 +118,36 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
     // The banded matrices of the wave's channels.  Row n of A is output (oy,
     // ox) = (n / 8, n % 8) of a block; K slot j of lane group g is, in plane
     // dz (matrix dz), window row g and column j, and in the last matrix plane
-    // g, row j / 2 and column 8 + j % 2 (lane group 3: the bias, against 1).
+    // j / 2, window row g and column 8 + j % 2 (slot 6 of lane group 0: the bias,
+    // against 1).
     v8h am[4][4];
     {
+        // A row of taps is 48 bits; a row of the matrix has them ox halves up
+        // (choosing each element by compares took 0.6 us of a small volume's step:
+        // 4 x 16 x 16 cells 9.4 us, now 8.6).
         const int oy = n >> 3, ox = n & 7;
+        const int dy = g - oy, row = min(max(dy, 0), 2);
+        const bool in = dy == row, high = ox >= 4;
+        const int up = 16 * (ox & 3);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const _Float16 *w = cw[4 * wave + q];
+            v4u last = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
-                const int r = g - oy;                        // dy + 1
-                const int rc = min(max(r, 0), 2);
-                const _Float16 z = (_Float16)0.f;
-                const _Float16 w0 = r == rc ? w[m * kTapPlane + 3 * rc] : z;
-                const _Float16 w1 = r == rc ? w[m * kTapPlane + 3 * rc + 1] : z;
-                const _Float16 w2 = r == rc ? w[m * kTapPlane + 3 * rc + 2] : z;
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    am[q][m][j] = j == ox ? w0 : j == ox + 1 ? w1 : j == ox + 2 ? w2 : z;
+                const uint2 w = *reinterpret_cast<const uint2 *>(cw[4 * wave + q] + 4 * (3 * m + row));
+                const uint32_t w0 = in ? w.x : 0u, w1 = in ? w.y : 0u;
+                const uint64_t taps = (uint64_t)w1 << 32 | w0;
+                const uint64_t a = taps << up, over = (taps >> 1) >> (63 - up);
+                const v4u r = {high ? 0u : (uint32_t)a, high ? 0u : (uint32_t)(a >> 32),
+                               high ? (uint32_t)a : (uint32_t)over,
+                               high ? (uint32_t)(a >> 32) : (uint32_t)(over >> 32)};
+                am[q][m] = __builtin_bit_cast(v8h, r);
+                // columns 8, 9: taps 1 and 2 of output 7, tap 2 of output 6
+                last[m] = ox == 7 ? __builtin_amdgcn_alignbyte(w1, w0, 2) : ox == 6 ? w1 : 0u;
             }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int r = g - oy, d = 8 + j % 2 - ox;
-                const bool ok = j < 6 && r >= 0 && r <= 2 && d <= 2;
-                const int at = min(j / 2, 2) * kTapPlane + min(max(r, 0), 2) * 3 + min(d, 2);
-                const _Float16 v = w[at];
-                am[q][3][j] = ok ? v : (g == 0 && j == 6) ? w[kBias] : (_Float16)0.f;
-            }
+            const uint32_t bias = *reinterpret_cast<const uint32_t *>(cw[4 * wave + q] + kBias) & 0xffffu;
+            last[3] = g == 0 ? bias : 0u;
+            am[q][3] = __builtin_bit_cast(v8h, last);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -347,18 +350,16 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
         for (int m = 0; m < 3; ++m) {
             const _Float16 *pl = ring[(z + m + 3) & 3];
             uint4 v8[4];
-            uint32_t v2[4], w[5];
+            uint32_t v2[4];
+            uint2 w[3];      // taps 0 and 1 of a row, and tap 2
 #pragma unroll
-            for (int i = 0; i < 5; ++i)
-                w[i] = reinterpret_cast<const uint32_t *>(cw[c] + m * kTapPlane)[i];
+            for (int i = 0; i < 3; ++i)
+                w[i] = *reinterpret_cast<const uint2 *>(cw[c] + 4 * (3 * m + i));
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 v8[r] = *reinterpret_cast<const uint4 *>(pl + body + r * kRow);
                 v2[r] = *reinterpret_cast<const uint32_t *>(pl + tail + r * tail_row);
             }
-            // taps 0 and 1 of a row, and tap 2
-            const uint32_t w01[3] = {w[0], __builtin_amdgcn_alignbyte(w[2], w[1], 2), w[3]};
-            const float w2[3] = {(float)as_h2(w[1])[0], (float)as_h2(w[2])[1], (float)as_h2(w[4])[0]};
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 // cells 2 i, 2 i + 1 and 2 i + 1, 2 i + 2 of the row
@@ -373,8 +374,9 @@ __global__ __launch_bounds__(kThreads3, kBlocksPerCu3) void nca_step_3d_f16(cons
 #pragma unroll
                     for (int ox = 0; ox < 8; ++ox) {
                         const uint32_t v01 = ox & 1 ? odd[ox / 2] : even[ox / 2];
-                        sum[oy][ox] = __builtin_amdgcn_fdot2(as_h2(w01[dy]), as_h2(v01), sum[oy][ox], false);
-                        sum[oy][ox] = fmaf(w2[dy], (float)as_h2(even[ox / 2 + 1])[ox & 1], sum[oy][ox]);
+                        sum[oy][ox] = __builtin_amdgcn_fdot2(as_h2(w[dy].x), as_h2(v01), sum[oy][ox], false);
+                        sum[oy][ox] = fmaf((float)as_h2(w[dy].y)[0],
+                                           (float)as_h2(even[ox / 2 + 1])[ox & 1], sum[oy][ox]);
                     }
                 }
             }
