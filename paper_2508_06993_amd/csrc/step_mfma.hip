@@ -1560,8 +1560,18 @@ hipError_t launch_step2_mfma_up(const StepArgs &a, MfmaMlp mlp, Layout2d layout,
                : launch_pair_size<MlpF32State>(a, coarse, dst, img, coarse_w, fy, fx, true, stream);
 }
 
+// fp16 volumes of two planes of the 12 / 48 model stay on the generic kernel from
+// this many cells a plane on: its tiles are two planes, where a run of the 3D step
+// streams four or six for them.  Generic kernel and 3D step, us a step: 2 x 160 x
+// 160 cells 11.3, 10.5; 200^2 12.9, 13.4; 250^2 12.8, 14.6; 300^2 19.7, 21.8; 350 x
+// 400 27.6, 32.5; 800^2 83, 88; 1000 x 1500 182, 235.  One plane of 300^2 17.7,
+// 13.6, three 31.5, 22.7, four of 200^2 21.4, 17.1.
+constexpr int64_t kTwoPlanes = 32000;
+
 bool step_mfma_serves(const StepArgs &a, Layout2d layout) {
     if (is_c16(a)) return true;
+    if (a.ndim == 3 && a.dtype == Dtype::F16 && a.ext.d == 2 && a.ext.h * a.ext.w >= kTwoPlanes)
+        return false;
     return is_c12(a) && (a.ndim == 3 || uses_rows(a, layout)) && mfma_fits(a);
 }
 

@@ -2,6 +2,7 @@
 // from stdin, for the tests of the plans.
 //   block <dtype> <c> <h> <rows> <cols> <steps> <images> <same_parity> -> use tile launches
 //   bwd <ndim> <d> <rows> <cols> <steps> -> use tile launches rows (of gradient sums)
+//   serves <dtype> <c> <h> <d> <rows> <cols> -> whether the specialised kernels run a 3D step
 #include <cstdio>
 #include <cstring>
 
@@ -47,6 +48,12 @@ int main() {
             const StepArgs a = args("f32", ndim, 16, 64, d, rows, cols);
             std::printf("%d %d %d %lld\n", use ? 1 : 0, use ? p.tile : 0, use ? p.launches : 0,
                         use ? (long long)bwd_block_rows(a, p) : 0ll);
+        } else if (!std::strcmp(what, "serves")) {
+            int c, h;
+            long d, rows, cols;
+            if (std::scanf("%7s %d %d %ld %ld %ld", dtype, &c, &h, &d, &rows, &cols) != 6) return 1;
+            const StepArgs a = args(dtype, 3, c, h, d, rows, cols);
+            std::printf("%d\n", step_mfma_serves(a, Layout2d::Auto) ? 1 : 0);
         } else {
             return 1;
         }

@@ -14,7 +14,7 @@ import torch
 import paper_2508_06993_amd as octnca
 from paper_2508_06993_amd.runtime import upload_weights
 import numpy as np
-from synthetic import LevelWeights
+from synthetic import LevelWeights, VIDEO_2DT, make_weights, scaled
 
 pytestmark = pytest.mark.gpu
 
@@ -57,6 +57,28 @@ def test_steps_match_vector_kernel(shape, n_in, dtype):
         assert torch.isfinite(got).all()
         assert float((got - want).abs().max()) <= tol * max(1.0, float(want.abs().max()))
         assert torch.equal(got[..., :n_in], state.float()[..., :n_in])
+
+
+@pytest.mark.parametrize("n_in", [1, 3])
+@pytest.mark.parametrize("shape", [(2, 160, 160), (2, 181, 179), (2, 200, 200), (3, 181, 179)])
+def test_two_planes_of_the_small_model(shape, n_in):
+    """fp16 12/48 volumes on both sides of the line from which two planes run on
+    the generic kernel."""
+    wl = scaled(VIDEO_2DT, shape, n_in=n_in, channels=12, hidden=48, factors=(), steps=(1,))
+    weights = upload_weights(make_weights(wl, 3))[0]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    state = torch.randn(shape + (12,), generator=gen, device="cuda").half()
+    out = {}
+    for kernel in ("mfma", "valu"):
+        model = octnca.Model(ndim=3, n_in=n_in, channels=12, hidden=48, dtype="f16", kernel=kernel)
+        b0, b1 = state.clone(), torch.full_like(state, float("nan"))
+        assert octnca.octree_nca_run_level(model, b0, b1, weights, 1, 5, 0.5, 77) == 1
+        torch.cuda.synchronize()
+        out[kernel] = b1.float()
+    got, want = out["mfma"], out["valu"]
+    assert torch.isfinite(got).all()
+    assert float((got - want).abs().max()) <= 1e-2 * max(1.0, float(want.abs().max()))
+    assert torch.equal(got[..., :n_in], state.float()[..., :n_in])
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])

@@ -74,3 +74,11 @@ def test_3d_backward_sums_few_tiles_in_fp32(plans, d, rows, cols):
     tiles = -(-d // 4) * -(-rows // 8) * -(-cols // 8)
     use, _, _, sums = plans([("bwd", 3, d, rows, cols, 1)])[0]
     assert use and tiles <= 8 * sums and sums <= tiles
+
+
+@pytest.mark.parametrize("dtype,c,h,d,rows,cols,special", [
+    ("f16", 12, 48, 2, 200, 200, 0), ("f16", 12, 48, 2, 160, 160, 1), ("f16", 12, 48, 1, 500, 500, 1),
+    ("f16", 12, 48, 3, 200, 200, 1), ("f32", 12, 48, 2, 200, 200, 1), ("f16", 16, 64, 2, 200, 200, 1),
+    ("f16", 20, 100, 3, 200, 200, 0)])
+def test_volumes_of_two_planes(plans, dtype, c, h, d, rows, cols, special):
+    assert plans([("serves", dtype, c, h, d, rows, cols)])[0][0] == special
