@@ -106,6 +106,7 @@ hipError_t launch_step_pair_up(const StepArgs &a, const void *coarse, int coarse
 struct StepBlockPlan {
     int tile = 0;
     int launches = 0;
+    double us = 0;   // the model's time, of these launches or of one per step where those win
     int steps_of(int i, int steps) const { return steps / launches + (i < steps % launches); }
 };
 bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBlockPlan *plan,

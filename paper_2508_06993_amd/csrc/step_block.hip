@@ -465,6 +465,7 @@ bool step_block_plan(const StepArgs &a, bool tape, int steps, int images, StepBl
             }
         }
     }
+    plan->us = best;
     return use;
 }
 

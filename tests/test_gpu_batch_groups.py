@@ -4,7 +4,8 @@ the batch gives with one step per launch, image after image (kernel
 "mfma_1step"), bit for bit.  Batch sizes that leave parts of one image, a
 single level, uneven factors, a finest level past the shared launches' limit,
 step counts of both parities (the last image's coarse state sits in its own
-final state) and a workspace larger than needed.
+final state) and a workspace larger than needed; large images whose levels are
+worth sharing for many steps and not for one.
 """
 import pytest
 import torch
@@ -40,6 +41,8 @@ def _batch(model, images, factors, weights, steps, extra=0):
     (4, (36, 60), ((1, 2, 2), (1, 3, 5)), (6, 0, 5)),          # a level without steps
     (3, (700, 640), ((1, 2, 2), (1, 2, 2)), (3, 4, 5)),        # the finest level image by image
     (70, (8, 16), ((1, 2, 2),), (3, 12)),                      # more than one group
+    (2, (2048, 1536), ((1, 2, 2),) * 3, (1, 1, 1, 1)),         # too few steps to share
+    (3, (1024, 768), ((1, 2, 2),) * 3, (2, 9, 10, 8)),
 ])
 def test_batch_equals_single_steps(dtype, c, h, batch, hw, factors, steps):
     wl = scaled(TINY_2D, (1,) + hw, steps=steps, channels=c, hidden=h, factors=factors,
