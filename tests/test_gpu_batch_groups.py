@@ -5,13 +5,17 @@ the batch gives with one step per launch, image after image (kernel
 single level, uneven factors, a finest level past the shared launches' limit,
 step counts of both parities (the last image's coarse state sits in its own
 final state) and a workspace larger than needed; large images whose levels are
-worth sharing for many steps and not for one.
+worth sharing for many steps and not for one.  The 20/100 model has no
+multi-step launches and runs image by image: its images against the vector
+kernel's (their fire masks follow the image's index; fp32 states on fp16
+operands, 40 and 100 products of 11 bits a step, up to 30 steps: below 1e-2 of
+the largest value) and the first against a single inference.
 """
 import pytest
 import torch
 
 import paper_2508_06993_amd as octnca
-from paper_2508_06993_amd.runtime import upload_weights
+from paper_2508_06993_amd.runtime import Inference, upload_weights
 from synthetic import TINY_2D, make_weights, scaled
 
 pytestmark = pytest.mark.gpu
@@ -50,11 +54,17 @@ def test_batch_equals_single_steps(dtype, c, h, batch, hw, factors, steps):
     weights = upload_weights(make_weights(wl, 6))
     k = dict(ndim=2, n_in=3, dtype=dtype, channels=c, hidden=h)
     group = octnca.Model(**k)
-    single = octnca.Model(kernel="mfma_1step", **k) if c != 20 else octnca.Model(**k)
+    single = octnca.Model(kernel="mfma_1step" if c != 20 else "valu", **k)
     gen = torch.Generator(device="cuda").manual_seed(batch)
     images = torch.rand((batch, 1) + hw + (3,), generator=gen, device="cuda").to(group.torch_dtype)
     want = _batch(single, images, factors, weights, steps)
     for extra in (0, 1 << 20):
         got = _batch(group, images, factors, weights, steps, extra)
+        if c == 20:
+            scale = want[0].abs().amax(dim=(1, 2, 3, 4))
+            assert bool(((got[0] - want[0]).abs().amax(dim=(1, 2, 3, 4)) <= 1e-2 * scale).all())
+            first, seg = Inference(group, (1,) + hw, factors)(images[0], weights, steps, 0.5, 31)
+            assert torch.equal(got[0][0], first) and torch.equal(got[1][0], seg)
+            continue
         assert torch.equal(got[0].view(torch.uint8), want[0].view(torch.uint8))
         assert torch.equal(got[1], want[1])
