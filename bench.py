@@ -136,7 +136,7 @@ def step_source_sha256() -> str:
 
 
 def measured_traffic(wl, selector: str):
-    """HBM bytes per step launch from the profiler's FETCH_SIZE / WRITE_SIZE
+    """HBM bytes per launch unit of the steps from the profiler's FETCH_SIZE / WRITE_SIZE
     counters (each scaled by what it reads for a plain copy of known size),
     recorded in profiles/ together with the hash of the step kernel's sources;
     None when no record matches this workload, selector and source."""
@@ -458,11 +458,10 @@ def inference_record(wl, kernel: str, steps: int, warmup: int, sub: bool = False
         for l in range(L):
             if wl.steps[l] > 0:
                 step_ms += row[2 * l].elapsed_time(row[2 * l + 1])
-    # step-kernel launches of a pass as the library enqueues them (a launch
-    # runs one step, or two on large 2D fp32 levels)
-    launches = steps * sum(octnca.octree_nca_infer_launches(model, wl.extent, wl.factors,
-                                                            wl.steps))
-    avg_launch_ms = step_ms / launches
+    # launch units of the steps: launches of one step, or of two on large 2D
+    # fp32 levels; small 2D levels, which run several steps in a launch, count
+    # one per step
+    units = steps * sum(octnca.octree_nca_infer_launches(model, wl.extent, wl.factors, wl.steps))
     flop = algorithmic_flop_per_cell_step(wl) * cell_steps * steps
     byts = algorithmic_bytes_per_cell_step(wl) * cell_steps * steps
     achieved_tflops = flop / (step_ms * 1e-3) / 1e12
@@ -485,15 +484,15 @@ def inference_record(wl, kernel: str, steps: int, warmup: int, sub: bool = False
         "unit": unit,
         "frac": round(achieved / peak, 4),
         "traffic": measured_traffic(wl, kernel),
-        "traffic_unit": "bytes per launch (HBM, profiler counters)",
+        "traffic_unit": "bytes per launch unit (HBM, profiler counters)",
         "arithmetic": arith,
         "achieved_tflops": round(achieved_tflops, 3),
         "arith_peak_tflops": round(arith_peak, 1),
         "arith_frac": round(achieved_tflops / arith_peak, 4),
         "achieved_hbm_gbs": round(achieved_gbs, 1),
         "hbm_frac": round(achieved_gbs / HBM_PEAK_GBS, 4),
-        "avg_launch_ms": round(avg_launch_ms, 4),
-        "launches": launches,
+        "avg_unit_ms": round(step_ms / units, 4),
+        "launch_units": units,
         "flop_per_cell_step": algorithmic_flop_per_cell_step(wl),
         "bytes_per_cell_step": algorithmic_bytes_per_cell_step(wl),
     }

@@ -252,12 +252,12 @@ int octree_nca_infer(const octnca_model *model, const void *image, octnca_extent
                      float fire_rate, uint64_t seed, void *workspace, size_t workspace_bytes,
                      void *final_state, uint8_t *seg, void *const *level_events, void *stream);
 
-/* Step-kernel launches that octree_nca_infer enqueues for each level with the
- * model's step kernel (a measurement aid: the launches of a level add up to
- * its steps, one or two steps per launch; a launch that runs several steps of
- * a small 2D level counts one per step, as the single-step launches it stands
- * for).  The count depends only on the
- * arguments, not on the device.
+/* Launch units of the steps of each level with the model's step kernel (a
+ * measurement aid): one for each launch of one step, or of two steps on large
+ * 2D fp32 levels.  It is the number of step launches that octree_nca_infer
+ * enqueues except on small 2D levels, where a launch runs up to 10 steps and
+ * counts one unit per step.  The count depends only on the arguments, not on
+ * the device.
  *   launches  host, [L], written: launches[l] for level l (index 0 = finest).
  * Host only: enqueues nothing.  Errors: EINVAL (null pointer, a negative
  * step count), ESHAPE, EUNSUPPORTED. */

@@ -337,8 +337,9 @@ def octree_nca_workspace_bytes(model: Model, finest, factors, with_final_state=T
 
 
 def octree_nca_infer_launches(model: Model, finest, factors, steps) -> list:
-    """Step-kernel launches per level (index 0 = finest) that octree_nca_infer
-    enqueues with the model's step kernel."""
+    """Launch units of the steps per level (index 0 = finest) with the model's
+    step kernel: the step launches that octree_nca_infer enqueues, but one per
+    step on small 2D levels, where a launch runs several."""
     levels = len(factors) + 1
     out = (_I32 * levels)()
     st = lib().octree_nca_infer_launches(ctypes.byref(model.struct()), _extent(finest), levels,

@@ -154,7 +154,8 @@ StepArgs step_args(const octnca_model *m, const octnca_extent &e, const octnca_l
 
 // Launches that run steps t0 .. t1-1 of a level: one per step, or one per two
 // steps where the two-step kernel applies (a trailing odd step runs alone).
-// (Small 2D levels are planned by step_block_plan instead.)
+// (Small 2D levels are planned by step_block_plan instead; in the count of
+// octree_nca_infer_launches they take one unit per step.)
 int32_t level_launches(const StepArgs &a, int32_t t0, int32_t t1) {
     if (t1 <= t0) return 0;
     return step_pairs(a) ? (t1 - t0 + 1) / 2 : t1 - t0;

@@ -367,10 +367,11 @@ def test_train_workspace_and_step_validation(lib):
 
 
 def test_infer_launches_counts_two_step_launches():
-    """Host query of the launches octree_nca_infer enqueues: on the 184.5 MP
-    pyramid the three large levels run their 20 steps in 10 two-step launches,
-    the first fused with the upsample; an odd count adds one single step; the
-    smaller levels and the one-step selection run one launch per step."""
+    """Host query of the launch units of the steps: on the 184.5 MP pyramid the
+    three large levels run their 20 steps in 10 two-step launches, the first
+    fused with the upsample; an odd count adds one single step; the smaller
+    levels (also where several of their steps share a launch) and the one-step
+    selection count one per step."""
     m = octnca.Model(ndim=2, n_in=3)
     f = [(1, 2, 2)] * 5
     assert octnca.octree_nca_infer_launches(m, (1, 11264, 16384), f, [20] * 6) == \
@@ -395,10 +396,10 @@ def test_infer_launches_counts_two_step_launches():
 
 
 def test_infer_launches_of_the_other_model_sizes():
-    """The 12/48 model's fp32 2D steps take the row kernels of 16/64, two steps
-    per launch included; its fp16 steps, its 3D steps and the 20/100 model run
-    one step per launch (no upsample fusion in 3D fp32 and on the generic
-    kernel, so each level but the coarsest adds none)."""
+    """The 12/48 model's 2D steps take the row kernels of 16/64, fp32 states two
+    steps per launch included; its fp16 and 3D steps and the 20/100 model's count
+    one unit per step (no upsample fusion in this model's 3D steps and on the
+    generic kernel, so each level but the coarsest adds none)."""
     f = [(1, 2, 2)] * 5
     c12 = octnca.Model(ndim=2, n_in=3, channels=12, hidden=48)
     assert octnca.octree_nca_infer_launches(c12, (1, 11264, 16384), f, [20] * 6) == \
