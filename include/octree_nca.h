@@ -295,10 +295,15 @@ int octree_nca_infer_static(const octnca_model *model, const void *image, octnca
 
 /* Inference of a batch of images of the same extent (the paper's kernel
  * works on one image and notes that a batch is an extra dimension to iterate
- * over, supplement S3): image b runs exactly as octree_nca_infer, with the
- * fire-mask counter word 3 set to b, so the images draw independent masks and
- * image 0 reproduces octree_nca_infer.  The images run one after another on
- * `stream` and share one workspace.
+ * over, supplement S3): image b's results are those of octree_nca_infer with
+ * the fire-mask counter word 3 set to b, so the images draw independent masks
+ * and image 0 reproduces octree_nca_infer.  The images share one workspace and
+ * run one after another on `stream`, except that with final_states small 2D
+ * levels (of the models that run several steps a launch there: C = 16 and 12)
+ * run for up to 64 images in the same launches where that is faster.  Their
+ * states lie in the final_states of images still to come, so all of
+ * final_states is scratch, and no image's result is complete, until the whole
+ * call's work is.
  *   images       [batch][finest][n_in], storage type;  batch >= 1.
  *   workspace    device, >= octree_nca_workspace_bytes(..., final_states != NULL).
  *   final_states [batch][finest][C] written, or NULL.
