@@ -255,7 +255,9 @@ struct MlpF16M {
     static constexpr int NT = H / 16;   // hidden tiles computed (a smaller model: see MlpF16SM)
     static constexpr float kPerceptionScale = 1.f;
     // 12 / 48: a cell that does not fire keeps its stored bits whatever its
-    // update is, as on the generic kernel, which serves its other layout
+    // update is, and a sum is rounded to fp32 and then to fp16, as on the generic
+    // kernel, which serves this model's other layout (the fma and the conversion
+    // became one mixed-precision fma, with one rounding)
     static constexpr bool kSelectGate = C != kC;
     v8h w1[NT];
     v4f b1[NT];

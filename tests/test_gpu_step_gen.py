@@ -14,7 +14,7 @@ import torch
 import paper_2508_06993_amd as octnca
 from paper_2508_06993_amd.runtime import upload_weights
 import numpy as np
-from synthetic import LevelWeights, VIDEO_2DT, make_weights, scaled
+from synthetic import TINY_2D, VIDEO_2DT, LevelWeights, make_weights, scaled
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +93,23 @@ def test_values_that_are_not_finite_stay_local(value, channel):
         near[0, max(0, y - 1):y + 2, max(0, x - 1):x + 2] = True
     got = _run("mfma", dirty, weights, 1, 1, rate=1.0)
     assert torch.equal(got[~near], clean[~near])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(1, 33, 61), (1, 333, 451), (1, 1025, 800)])
+def test_layouts_of_the_small_model_give_the_same_bits(shape, dtype):
+    """The 12/48 model's 2D steps: tiles kept on chip or rows as the size asks,
+    rows, and the generic kernel's tiles sum in the same order and round once."""
+    wl = scaled(TINY_2D, shape, n_in=3, channels=12, hidden=48, dtype=dtype, factors=(), steps=(1,))
+    weights = upload_weights(make_weights(wl, 3))[0]
+    out = []
+    for kernel in ("mfma", "mfma_rows,mfma_1step", "mfma_tiles"):
+        model = octnca.Model(ndim=2, n_in=3, channels=12, hidden=48, dtype=dtype, kernel=kernel)
+        gen = torch.Generator(device="cuda").manual_seed(7)
+        b0 = torch.randn(shape + (12,), generator=gen, device="cuda").to(model.torch_dtype)
+        b1 = torch.full_like(b0, float("nan"))
+        assert octnca.octree_nca_run_level(model, b0, b1, weights, 1, 3, 0.5, 99) == 1
+        torch.cuda.synchronize()
+        out.append(b1)
+    for other in out[1:]:
+        assert torch.equal(out[0].view(torch.uint8), other.view(torch.uint8))
