@@ -79,6 +79,18 @@ def algorithmic_bytes_per_cell_step(wl) -> int:
     return (wl.channels + wl.channels - wl.n_in) * eb
 
 
+def perceives_on_mfma(wl) -> bool:
+    """The fp16 3D step of the 16 / 64 model (with fp16 MLP operands)."""
+    return wl.dtype == "f16" and wl.ndim == 3 and (wl.channels, wl.hidden) == (16, 64)
+
+
+def mfma_kernel(wl) -> str:
+    """Matrix-core step kernel(s) of a workload with the default operands."""
+    if (wl.channels, wl.hidden) == (20, 100):
+        return "nca_step_gen"
+    return "nca_step_3d_f16" if perceives_on_mfma(wl) else "nca_step_mfma"
+
+
 def step_kernel_arithmetic(wl, kernel: str):
     """(kernel name, arithmetic of its MLP contraction, that arithmetic's
     MI355X peak in TFLOP/s) for a step-kernel name of ``Model(kernel=...)``."""
@@ -88,11 +100,11 @@ def step_kernel_arithmetic(wl, kernel: str):
     if "mfma_f32" in names:
         return "nca_step_mfma / fp32 MFMA", "fp32 MFMA", FP32_MFMA_PEAK_TFLOPS
     if "mfma_f16" in names or (wl.dtype == "f16" and "mfma_bf16x3" not in names):
-        return "nca_step_mfma / fp16 MFMA", "fp16 MFMA", FP16_MFMA_PEAK_TFLOPS
+        return f"{mfma_kernel(wl)} / fp16 MFMA", "fp16 MFMA", FP16_MFMA_PEAK_TFLOPS
     if "mfma_bf16x3" in names:
         return "nca_step_mfma / split-bf16 MFMA", "bf16 MFMA (3 products per fp32 product)", \
             BF16_MFMA_PEAK_TFLOPS
-    return "nca_step_mfma / scaled-fp16 MFMA", \
+    return f"{mfma_kernel(wl)} / scaled-fp16 MFMA", \
         "fp16 MFMA (fp16 activations x split fp16 weights, 2 products per fp32 product)", \
         FP16_MFMA_PEAK_TFLOPS
 
@@ -108,7 +120,7 @@ def arithmetic_label(wl, kernel: str) -> str:
     if "mfma_bf16x3" in names:
         return f"{store}; perception fp32 FMA; MLP split-bf16 MFMA (3 products), fp32 accumulate"
     if wl.dtype == "f16":
-        pk = "packed fp16 FMA" if wl.ndim == 3 else "fp32 FMA"
+        pk = "fp16 MFMA, fp32 accumulate" if perceives_on_mfma(wl) else "fp32 FMA"
         return f"{store}; perception {pk}; MLP fp16 MFMA, fp32 accumulate"
     return (f"{store}; perception fp32 FMA; MLP fp16 MFMA on activations scaled by 2^-8 and "
             "rounded to fp16 x weights split into fp16 hi + lo, fp32 accumulate")

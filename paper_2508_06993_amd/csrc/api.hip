@@ -31,8 +31,8 @@ int check_model(const octnca_model *m) {
     if (m->ndim != 2 && m->ndim != 3) return OCTNCA_EUNSUPPORTED;
     // C / H: the paper's 16 / 64 and the 12 / 48 and 20 / 100 of its ablation
     // (supplement S10); every size runs on the matrix cores (the specialised
-    // kernels for 16 / 64 and fp32 12 / 48, a generic kernel otherwise) and on
-    // the vector kernel
+    // kernels for 16 / 64 and, in most cases, 12 / 48, a generic kernel
+    // otherwise) and on the vector kernel
     const bool size_ok = (m->channels == 16 && m->hidden == 64) ||
                          (m->channels == 12 && m->hidden == 48) ||
                          (m->channels == 20 && m->hidden == 100);
@@ -1188,9 +1188,9 @@ namespace octnca {
 // caller's octnca_model); nothing here reads the environment.
 hipError_t launch_step(const StepArgs &a, const void *src, void *dst, hipStream_t stream) {
     if (a.kc.valu) return launch_step_valu(a, src, dst, stream);
-    // the specialised matrix-core kernels serve C = 16, H = 64 and the 2D
-    // fp32 row layout of C = 12, H = 48; the other steps of the ablation's
-    // sizes run on the generic matrix-core kernel
+    // the specialised matrix-core kernels serve C = 16, H = 64 and most steps of
+    // C = 12, H = 48; the other steps of the ablation's sizes run on the generic
+    // matrix-core kernel
     if (!step_mfma_serves(a, a.kc.layout)) return launch_step_gen(a, src, dst, stream);
     return launch_step_mfma(a, a.kc.mlp, a.kc.layout, src, dst, stream);
 }

@@ -81,8 +81,9 @@ hipError_t launch_step_up(const StepArgs &a, const void *coarse, int coarse_h, i
                           int fz, int fy, int fx, const void *img, void *dst,
                           hipStream_t stream);
 hipError_t launch_step_valu(const StepArgs &a, const void *src, void *dst, hipStream_t stream);
-// Matrix-core step for the model sizes other than C = 16, H = 64 (the
-// ablation's 12 / 48 and 20 / 100): whether it serves `a`, and the launch.
+// Generic matrix-core step for the model sizes other than C = 16, H = 64 (the
+// ablation's 12 / 48, where the specialised steps do not run it, and 20 / 100):
+// whether it serves `a`, and the launch.
 bool step_gen_serves(const StepArgs &a);
 hipError_t launch_step_gen(const StepArgs &a, const void *src, void *dst, hipStream_t stream);
 // Whether launch_step_pair runs steps a.step and a.step + 1 in one launch, and
@@ -174,9 +175,10 @@ size_t mse_workspace_doubles(int64_t cells);
 hipError_t launch_readout_mse(const float *state, const float *target, int64_t cells, int channels,
                               float *grad, double *loss, double *ws, hipStream_t stream);
 hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t stream);
-// The specialised matrix-core steps: every step of C = 16, H = 64 models and
-// the 2D fp32 steps of C = 12, H = 48 models in the row layout (default
-// operand policy); step_mfma_serves says whether launch_step_mfma runs `a`.
+// The specialised matrix-core steps: every step of C = 16, H = 64 models and,
+// with the default operand policy, of C = 12, H = 48 models the 2D steps in the
+// row layout and the 3D ones (but fp16 volumes of two large planes);
+// step_mfma_serves says whether launch_step_mfma runs `a`.
 bool step_mfma_serves(const StepArgs &a, Layout2d layout);
 hipError_t launch_step_mfma(const StepArgs &a, MfmaMlp mlp, Layout2d layout, const void *src,
                             void *dst, hipStream_t stream);

@@ -1,7 +1,8 @@
 // Fused NCA step on the matrix cores for any model size C / H with C a
 // multiple of 4 (Sec. 3.1; supplement S3, Listing 1).  It serves the other
-// sizes of the paper's ablation (supplement S10: C / H = 12 / 48 and
-// 20 / 100); the C = 16, H = 64 model has its own specialised kernels.
+// sizes of the paper's ablation (supplement S10): C / H = 20 / 100, and of 12 /
+// 48 the 2D tile layout and what else the specialised kernels of C = 16, H = 64
+// do not take.
 //
 // Layout (generalising the 16 / 64 kernels' lane mapping):
 //   lane l of a wave -> cell n = l % 16 of a 16-cell group and lane group
