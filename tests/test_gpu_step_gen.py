@@ -81,6 +81,29 @@ def test_two_planes_of_the_small_model(shape, n_in):
     assert torch.equal(got[..., :n_in], state.float()[..., :n_in])
 
 
+def test_rows_too_wide_for_the_specialised_step():
+    """fp32 12/48 volumes whose 18 rows of 64-byte cells pass 2^32 bytes run on
+    the generic kernel, whose offsets are within 2 x 4 x 32 tiles."""
+    shape = (1, 1, 3_800_003)
+    assert 18 * 64 * shape[2] >= 2 ** 32
+    wl = scaled(VIDEO_2DT, shape, n_in=1, channels=12, hidden=48, dtype="f32", factors=(),
+                steps=(1,))
+    weights = upload_weights(make_weights(wl, 3))[0]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    state = torch.randn(shape + (12,), generator=gen, device="cuda")
+    out = []
+    for kernel in ("mfma", "valu"):
+        model = octnca.Model(ndim=3, n_in=1, channels=12, hidden=48, kernel=kernel)
+        b0, b1 = state.clone(), torch.full_like(state, float("nan"))
+        assert octnca.octree_nca_run_level(model, b0, b1, weights, 1, 1, 0.5, 77) == 1
+        torch.cuda.synchronize()
+        out.append(b1)
+    got, want = out
+    assert torch.isfinite(got).all()
+    assert float((got - want).abs().max()) <= 4e-3 * max(1.0, float(want.abs().max()))
+    assert torch.equal(got[..., :1], state[..., :1])
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 @pytest.mark.parametrize("channel", [2, 17])   # a full quad's, the last quad's
 def test_values_that_are_not_finite_stay_local(value, channel):
