@@ -222,21 +222,20 @@ inline int device_cus() {
     return n;
 }
 
-// Output planes per 3D work item, chosen per launch: the run length r in
-// 1 .. max_run that minimises ceil(items(r) / slots) * (min(r, depth) + extra,
-// rounded up to whole groups), the work of the most loaded block slot
-// (grid-stride rounds times the planes a work item streams, `extra` halo and
-// set-up planes included); ties go to the longer run.  Short runs spread small
-// levels over the chip at the cost of reading their halo planes again; long
-// runs stream large levels with little re-reading.  group: a plane loop that
-// is unrolled streams whole groups of planes.
-inline int pick_zrun(int64_t tiles, int64_t depth, int64_t slots, int extra, int group,
-                     int max_run) {
+// Output planes per work item of the fp32-ring 3D step, chosen per launch: the
+// run length r in 1 .. max_run that minimises ceil(items(r) / slots) *
+// (min(r, depth) + 2, rounded up to whole groups of three), the work of the
+// most loaded block slot (grid-stride rounds times the planes a work item
+// streams, its halo planes included; the plane loop is unrolled three times);
+// ties go to the longer run.  Short runs spread small levels over the chip at
+// the cost of reading their halo planes again; long runs stream large levels
+// with little re-reading.
+inline int pick_zrun(int64_t tiles, int64_t depth, int64_t slots, int max_run) {
     int best = 1;
     int64_t best_cost = INT64_MAX;
     for (int r = 1; r <= max_run; ++r) {
         const int64_t items = tiles * ((depth + r - 1) / r);
-        const int64_t planes = (std::min<int64_t>(r, depth) + extra + group - 1) / group * group;
+        const int64_t planes = (std::min<int64_t>(r, depth) + 4) / 3 * 3;
         const int64_t cost = (items + slots - 1) / slots * planes;
         if (cost <= best_cost) {
             best_cost = cost;
@@ -251,5 +250,8 @@ inline int pick_zrun(int64_t tiles, int64_t depth, int64_t slots, int extra, int
 // fused with the upsample from the coarse state src (planes of cdh x cdw cells).
 hipError_t launch_step_3d_f16(const StepArgs &a, const void *src, void *dst, const void *img,
                               int cdh, int cdw, int fz, int fy, int fx, hipStream_t stream);
+// Its run length (planes per work item, at most max_run) for a level of `depth`
+// planes of `tiles` tiles on a device of `cus` CUs.
+int step_3d_f16_run(int64_t tiles, int64_t depth, int64_t cus, int max_run);
 
 }  // namespace octnca

@@ -1485,7 +1485,7 @@ hipError_t launch_3d(const StepArgs &a, const void *src, void *dst, hipStream_t 
         const int tiles_x = (int)((a.ext.w + kTileW - 1) / kTileW);
         const int tiles_y = (int)((a.ext.h + k3TY - 1) / k3TY);
         const int64_t slots = (int64_t)device_cus() * kBlocksPerCu;
-        const int zrun = pick_zrun((int64_t)tiles_x * tiles_y, a.ext.d, slots, 2, 3, k3ZRun);
+        const int zrun = pick_zrun((int64_t)tiles_x * tiles_y, a.ext.d, slots, k3ZRun);
         const int64_t zruns = (a.ext.d + zrun - 1) / zrun;
         const int64_t items = (int64_t)tiles_x * tiles_y * zruns;
         if (items == 0) return hipSuccess;

@@ -3,6 +3,7 @@
 //   block <dtype> <c> <h> <rows> <cols> <steps> <images> <same_parity> -> use tile launches
 //   bwd <ndim> <d> <rows> <cols> <steps> -> use tile launches rows (of gradient sums)
 //   serves <dtype> <c> <h> <d> <rows> <cols> -> whether the specialised kernels run a 3D step
+//   run <d> <rows> <cols> -> planes of a work item of the fp16 3D step (256 CUs)
 #include <cstdio>
 #include <cstring>
 
@@ -54,6 +55,11 @@ int main() {
             if (std::scanf("%7s %d %d %ld %ld %ld", dtype, &c, &h, &d, &rows, &cols) != 6) return 1;
             const StepArgs a = args(dtype, 3, c, h, d, rows, cols);
             std::printf("%d\n", step_mfma_serves(a, Layout2d::Auto) ? 1 : 0);
+        } else if (!std::strcmp(what, "run")) {
+            long d, rows, cols;
+            if (std::scanf("%ld %ld %ld", &d, &rows, &cols) != 3) return 1;
+            std::printf("%d\n", step_3d_f16_run((rows + 7) / 8 * ((cols + 31) / 32), d, 256,
+                                                cols % 8 == 0 ? 256 : 128));
         } else {
             return 1;
         }

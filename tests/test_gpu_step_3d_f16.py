@@ -1,7 +1,7 @@
 """The fp16 3D step's perception on the matrix cores (step_3d_f16.hip): one
 step and several against the vector kernel, whose perception sums the same
 fp16 states and fp32 taps one by one in fp32, at sizes around its 8 x 32 tiles
-and 2 x 8 blocks, with runs of one plane and (48 x 120 x 216, 60 x 108 x 212,
+and 2 x 8 blocks, with runs of one and two planes and (48 x 120 x 216, 60 x 108 x 212,
 300 x 40 x 64) of 6 and 12; and cells that are not finite, which must reach their
 own 3 x 3 x 3 neighbours only, with the values that the vector kernel gives, in
 the plain step and in those fused with the upsample and the readout.

@@ -82,3 +82,12 @@ def test_3d_backward_sums_few_tiles_in_fp32(plans, d, rows, cols):
     ("f16", 20, 100, 3, 200, 200, 0)])
 def test_volumes_of_two_planes(plans, dtype, c, h, d, rows, cols, special):
     assert plans([("serves", dtype, c, h, d, rows, cols)])[0][0] == special
+
+
+@pytest.mark.parametrize("d,rows,cols,run", [
+    (14, 243, 64, 4), (57, 106, 32, 4), (34, 65, 40, 3), (22, 66, 56, 2), (4, 30, 304, 1),
+    (1, 1, 1, 1), (60, 108, 212, 12), (48, 120, 216, 12), (1800, 240, 432, 106), (1800, 60, 108, 113)])
+def test_runs_of_the_fp16_3d_step(plans, d, rows, cols, run):
+    """Where it costs little, every work item has a CU of its own; the runs of
+    large levels fill the block slots."""
+    assert plans([("run", d, rows, cols)])[0][0] == run
